@@ -91,9 +91,10 @@ CTREX_API int ctrex_create(ctrex_ctx **out, int device);
  * the reconstruction control, here the caller).  ctrex_scratch_bytes returns
  * the bytes the calls of the current geometry (and cylindrical domain, if
  * set) need for view lists of up to n_views entries (n_views <= 0: n_proj):
- * the correction volume (4 bytes per voxel), a 16-bit shadow (2), the
- * copies of the volume the rays gather from (32 for FP32, 16 for 16-bit;
- * the backprojector's 64-bit integer sums, 8 per voxel, reuse that region)
+ * the correction volume (4 bytes per voxel), a 16-bit shadow (2), a region
+ * (32 for FP32, 16 for 16-bit) for the copies of the volume the rays gather
+ * from (half of it; the backprojector's 64-bit integer sums, 8 per voxel,
+ * reuse the region)
  * and the residual partials (8 per 16x16 detector tile per view).
  * CTREX_ESTATE without a geometry.
  * ctrex_set_scratch attaches `bytes` of device memory at `dev` (NULL, 0
@@ -163,10 +164,10 @@ CTREX_API int ctrex_set_voxel_weights(ctrex_ctx *ctx, const float *w_dev);
  * vol_dtype and `sino` sino_dtype; the sinogram is overwritten.  With an
  * empty list (n_views == 0) nothing happens and the pointers may be NULL.
  * The rays gather from copies of `vol` written into the attached scratch at
- * the start of the call: two corner-packed copies (x- and y-fastest; each
- * element holds a voxel's four corner values in its z slice: 16 bytes for
- * float32, 8 bytes for 16-bit storage).  The results do not depend on which
- * copy a ray reads.
+ * the start of the call: two pair-packed copies (x- and y-fastest; each
+ * element holds a voxel's value and its neighbour's along the slower of the
+ * two axes: 8 bytes for float32, 4 bytes for 16-bit storage).  The results do
+ * not depend on which copy a ray reads.
  */
 CTREX_API int ctrex_forward_project(ctrex_ctx *ctx, const void *vol, int32_t vol_dtype, void *sino,
                           int32_t sino_dtype, const int32_t *views, int32_t n_views,
@@ -262,8 +263,8 @@ CTREX_API int ctrex_sirt_workspace_bytes(const ctrex_ctx *ctx, int32_t n_views, 
  * workspace).  The context remembers up to 64 (workspace, view list) pairs,
  * so ordered subsets — one workspace per subset, cycled — keep their
  * weights.  The volume-sized intermediates (the correction volume, a 16-bit
- * shadow and the copies of vol the rays gather from: 32 bytes per voxel in
- * FP32, 16 with a 16-bit gather) live in the attached scratch, shared by all
+ * shadow and the copies of vol the rays gather from: a region of 32 bytes per
+ * voxel in FP32, 16 with a 16-bit gather) live in the attached scratch, shared by all
  * workspaces.  With a
  * BF16/F16 gather flag the rays march a 16-bit shadow of vol, refreshed
  * after every update, while the update itself stays FP32.  The correction

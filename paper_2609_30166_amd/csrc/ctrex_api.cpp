@@ -32,11 +32,9 @@ constexpr size_t kAlign = 256;
 constexpr int kResidCap = 1024;
 constexpr size_t kMaxLists = 64;
 constexpr size_t kMaxWeightSets = 64;
-// FP32 volumes are gathered from corner-packed copies (two 16-byte loads per
-// sample instead of four 8-byte ones); 16-bit volumes from the plain copies.
-constexpr bool kPackedCorners = true;
-// The same for 16-bit volumes: two corner-packed copies of 8 bytes per voxel.
-constexpr bool kPacked16 = true;
+// Bytes of attached scratch that the gather copies may take per voxel of an
+// FP32 (16-bit) volume.  The pair-packed copies fill half of it.
+constexpr size_t kCopyBytes32 = 32, kCopyBytes16 = 16;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -216,8 +214,8 @@ struct SirtLayout {
 
 // The caller's scratch (ctrex_set_scratch), as the Cartesian projector calls
 // use it: the correction volume z, a 16-bit shadow, one region shared by the
-// gather copies of the forward projector (FP32: two corner-packed copies of
-// 16 bytes per voxel; 16-bit: 8 bytes each) and the backprojector's
+// gather copies of the forward projector (FP32: two pair-packed copies of 8
+// bytes per voxel; 16-bit: 4 bytes each) and the backprojector's
 // per-chunk partial volumes (never live at the same time), and the residual
 // partials.  Each call needs the prefix up to the last region it uses.
 struct ProjScratch {
@@ -247,8 +245,7 @@ SirtLayout sirt_layout(const ctrex_ctx *c, int32_t n_views) {
 
 size_t packed_bytes(const ctrex_ctx *c, int vol_dtype) {
     const size_t vox = static_cast<size_t>(c->nx) * c->ny * c->nz;
-    if (vol_dtype == F32) return kPackedCorners ? 2 * sizeof(float4) * vox : 4 * vox;
-    return kPacked16 ? 2 * sizeof(uint2) * vox : 2 * vox;
+    return (vol_dtype == F32 ? kCopyBytes32 : kCopyBytes16) * vox;
 }
 
 ProjScratch proj_scratch(const ctrex_ctx *c, int32_t n_views) {
@@ -281,25 +278,11 @@ struct CylScratch {
 int make_gather_copies(ctrex_ctx *c, const void *vol, int vol_dtype, void *dst, FpExtra &ex,
                        hipStream_t s) {
     const size_t vox = static_cast<size_t>(c->nx) * c->ny * c->nz;
-    if (kPackedCorners && vol_dtype == F32) {
-        // corner-packed copies, x- and y-fastest
-        float4 *p4 = static_cast<float4 *>(dst);
-        CTREX_HIP(c, launch_pack_corners(static_cast<const float *>(vol), p4, p4 + vox, c->nx,
-                                         c->ny, c->nz, s));
-        ex.p4 = p4;
-        ex.p4t = p4 + vox;
-    } else if (kPacked16 && vol_dtype != F32) {
-        // 16-bit corner-packed copies, x- and y-fastest
-        uint2 *p2 = static_cast<uint2 *>(dst);
-        CTREX_HIP(c, launch_pack_corners16(static_cast<const uint16_t *>(vol), p2, p2 + vox,
-                                           c->nx, c->ny, c->nz, s));
-        ex.p2 = p2;
-        ex.p2t = p2 + vox;
-    } else {
-        // y-fastest copy for the projections whose rays run mainly along x
-        CTREX_HIP(c, launch_transpose_xy(vol, dst, vol_dtype, c->nx, c->ny, c->nz, s));
-        ex.vol_t = dst;
-    }
+    const size_t pair = vol_dtype == F32 ? sizeof(float2) : sizeof(uint32_t);
+    char *px = static_cast<char *>(dst), *py = px + pair * vox;
+    CTREX_HIP(c, launch_pack_pairs(vol, vol_dtype, px, py, c->nx, c->ny, c->nz, s));
+    ex.px = px;
+    ex.py = py;
     return CTREX_OK;
 }
 
@@ -308,7 +291,7 @@ CylScratch cyl_scratch(const ctrex_ctx *c) {
     CylScratch l;
     l.z = 0;
     l.packed = align_up(4 * vox);
-    l.total = align_up(l.packed + (kPackedCorners ? sizeof(float4) * vox : 0));
+    l.total = align_up(l.packed + sizeof(float4) * vox);
     return l;
 }
 
@@ -872,31 +855,13 @@ int ctrex_sirt_iterate(ctrex_ctx *c, float *vol, const void *sino, int32_t sino_
         CTREX_HIP(c, launch_convert(vol, F32, shadow, gdt, vox, s));
         gather = shadow;
     }
-    void *vt = sc + SL.shared;
-    const bool packed = kPackedCorners && gdt == F32;
-    const bool packed16 = kPacked16 && gdt != F32;
-    float4 *p4 = static_cast<float4 *>(vt);
-    uint2 *p2 = static_cast<uint2 *>(vt);
-    auto refresh_copies = [&]() -> hipError_t {
-        if (packed) return launch_pack_corners(vol, p4, p4 + vox, c->nx, c->ny, c->nz, s);
-        if (packed16)
-            return launch_pack_corners16(static_cast<const uint16_t *>(gather), p2, p2 + vox,
-                                         c->nx, c->ny, c->nz, s);
-        return launch_transpose_xy(gather, vt, gdt, c->nx, c->ny, c->nz, s);
+    FpExtra ex{sino, Rw, partials};
+    auto refresh_copies = [&]() {
+        return make_gather_copies(c, gather, gdt, sc + SL.shared, ex, s);
     };
-    CTREX_HIP(c, refresh_copies());
+    if ((st = refresh_copies()) != CTREX_OK) return st;
     std::vector<double> host_norms;
     if (resid_norms) host_norms.reserve(n_iter);
-    FpExtra ex{sino, Rw, partials};
-    if (packed) {
-        ex.p4 = p4;
-        ex.p4t = p4 + vox;
-    } else if (packed16) {
-        ex.p2 = p2;
-        ex.p2t = p2 + vox;
-    } else {
-        ex.vol_t = vt;
-    }
     for (int32_t k = 0; k < n_iter; ++k) {
         PhaseTimer t_fp{c, s, nullptr, 0}, t_bp{c, s, nullptr, 1}, t_up{c, s, nullptr, 2};
         CTREX_HIP(c, t_fp.begin());
@@ -912,7 +877,7 @@ int ctrex_sirt_iterate(ctrex_ctx *c, float *vol, const void *sino, int32_t sino_
         CTREX_HIP(c, t_up.begin());
         CTREX_HIP(c, launch_update(vol, z, Cw, c->d_vw, alpha, (flags & CTREX_NONNEG) ? 1 : 0,
                                    gdt != F32 ? shadow : nullptr, gdt, vox, s));
-        if (k + 1 < n_iter) CTREX_HIP(c, refresh_copies());
+        if (k + 1 < n_iter && (st = refresh_copies()) != CTREX_OK) return st;
         CTREX_HIP(c, t_up.end());
         if (resid_norms && ((k + 1) % kResidCap == 0 || k + 1 == n_iter)) {
             const int cnt = (k % kResidCap) + 1;
@@ -1250,7 +1215,7 @@ int ctrex_forward_project_cyl(ctrex_ctx *c, const void *vol, int32_t vol_dtype, 
     if (!vol || !sino) return fail(c, CTREX_EINVAL, "vol and sino must be device pointers");
     if ((st = check_blocks(c, nv)) != CTREX_OK) return st;
     FpExtra ex{nullptr, nullptr, nullptr};
-    if (kPackedCorners && vol_dtype == F32) {
+    if (vol_dtype == F32) {
         const CylScratch CL = cyl_scratch(c);
         void *scr;
         if ((st = ctx_scratch(c, CL.total, &scr))) return st;
@@ -1388,13 +1353,12 @@ int ctrex_sirt_iterate_cyl(ctrex_ctx *c, float *vol, const void *sino, int32_t s
     std::vector<double> host_norms;
     if (resid_norms) host_norms.reserve(n_iter);
     FpExtra ex{sino, Rw, partials};
-    float4 *p4 = kPackedCorners ? reinterpret_cast<float4 *>(static_cast<char *>(scr) + CL.packed)
-                                : nullptr;
+    float4 *p4 = reinterpret_cast<float4 *>(static_cast<char *>(scr) + CL.packed);
     ex.p4 = p4;
     for (int32_t k = 0; k < n_iter; ++k) {
         PhaseTimer t_fp{c, s, nullptr, 0}, t_bp{c, s, nullptr, 1}, t_up{c, s, nullptr, 2};
         CTREX_HIP(c, t_fp.begin());
-        if (p4) CTREX_HIP(c, launch_pack_polar(vol, p4, c->cyl_nr, c->cyl_nphi, c->cyl_nz, s));
+        CTREX_HIP(c, launch_pack_polar(vol, p4, c->cyl_nr, c->cyl_nphi, c->cyl_nz, s));
         CTREX_HIP(c, launch_forward_cyl(g, cg, vol, F32, r, sino_dtype, FP_CORRECT, ex, s));
         CTREX_HIP(c, t_fp.end());
         CTREX_HIP(c, launch_sum_partials(partials, g.total_blocks, resid + (k % kResidCap), s));

@@ -64,17 +64,16 @@ struct FpExtra {
     const float *R;      // detector weights (FP_CORRECT); nullptr: the constant rscale
     double *partials;    // [total_blocks] (FP_CORRECT, FP_RESIDUAL)
     float rscale = 1.0f; // FP_CORRECT without R: out = rscale (b - A vol)
-    const void *vol_t = nullptr;  // optional y-fastest copy [nz][nx][ny] of the volume
-    // optional corner-packed copies of an FP32 volume (element (x, y, z) = the
-    // four corners v(x, y), v(x+1, y), v(x, y+1), v(x+1, y+1) of slice z):
-    // x-fastest [nz][ny][nx] and y-fastest [nz][nx][ny]; when set they replace
-    // vol and vol_t in the gathers
+    // pair-packed copies of the volume the rays gather from (all modes but
+    // FP_RECIP_ONES, unless the LDS tubes are on): an element holds two
+    // values, so a 16-byte (FP32) or 8-byte (16-bit) load of two consecutive
+    // elements gives the four corners of a slice.  px: x-fastest
+    // [nz][ny][nx], element (x, y, z) = v(x, y), v(x, y+1); py: y-fastest
+    // [nz][nx][ny], element (y, x, z) = v(x, y), v(x+1, y)
+    const void *px = nullptr;
+    const void *py = nullptr;
+    // cylindrical domain: corner-packed copy of an FP32 polar volume
     const float4 *p4 = nullptr;
-    const float4 *p4t = nullptr;
-    // the same for a 16-bit volume: element (x, y, z) = the four 16-bit
-    // corners in the order above, two to a 32-bit word, low half first
-    const uint2 *p2 = nullptr;
-    const uint2 *p2t = nullptr;
 };
 
 // Backprojection modes.
@@ -137,16 +136,9 @@ hipError_t launch_recip(float *a, size_t n, hipStream_t stream);
 // x <- x + alpha C w z (w optional voxel weights), clamp, 16-bit shadow
 hipError_t launch_update(float *x, const float *z, const float *C, const float *w, float alpha,
                          int nonneg, void *shadow, int shadow_dtype, size_t n, hipStream_t stream);
-// dst = src with x and y exchanged ([nz][ny][nx] -> [nz][nx][ny]); dtype
-// gives the element size.
-hipError_t launch_transpose_xy(const void *src, void *dst, int dtype, int nx, int ny, int nz,
-                               hipStream_t s);
-// p4 / p4t = the corner-packed copies of FpExtra (either may be null).
-hipError_t launch_pack_corners(const float *vol, float4 *p4, float4 *p4t, int nx, int ny, int nz,
-                               hipStream_t s);
-// The same corner-packed copies of a 16-bit volume (BF16 or F16 bits).
-hipError_t launch_pack_corners16(const uint16_t *vol, uint2 *p2, uint2 *p2t, int nx, int ny,
-                                 int nz, hipStream_t s);
+// px / py = the pair-packed copies of FpExtra of a volume of storage type dtype.
+hipError_t launch_pack_pairs(const void *vol, int dtype, void *px, void *py, int nx, int ny, int nz,
+                             hipStream_t s);
 // Corner-packed copy of a polar volume [nz][nphi][nr]: element (k, j, a) holds
 // v(a, j), v(a+1, j), v(a, j+1), v(a+1, j+1) of slice k, the angle periodic.
 hipError_t launch_pack_polar(const float *vol, float4 *p4, int nr, int nphi, int nz,

@@ -26,18 +26,19 @@ namespace {
 using namespace dev;
 
 // ------------------------------------------------------- forward kernel ----
-// Gather from a corner-packed copy: the eight corners of a sample are the two
-// 16-byte elements of its lower corner in slices z and z + 1, holding the
-// values of the pair loads of `gather` / `gather_t` in the same order.
-__device__ __forceinline__ float gather_p4(const float4 *__restrict__ p4, const VolDims &d,
-                                           const Corner &k) {
-    const float4 a = p4[k.base];
-    const float4 b = p4[k.base + d.nxy];
-    return blend(k, a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w);
-}
+// Gather from a pair-packed copy: the four corners of a sample's cell in slice
+// z are two consecutive elements (x, x + 1; y-fastest: y, y + 1), one 16-byte
+// load of an FP32 copy (8-byte aligned) or one 8-byte load of a 16-bit copy
+// (4-byte aligned); slice z + 1 is the second load.  The gather is bound by
+// the L1: an element twice the voxel's size (an element holding all four
+// corners, four times the size, was aligned but filled the L1 with copies of
+// the same values) took a SIRT step over 180 of 720 views of 768^2 at 512^3
+// from 564 to 544 ms in FP32, and 72 views with 16-bit storage from 227 to
+// 207 ms, results bitwise identical.
+typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
-// 16-bit volumes: the four corners of a slice are one 8-byte element, two to a
-// 32-bit word (low half first), widened exactly as `ld` widens them.
+// 16-bit values two to a word (low half first), widened exactly as `ld` does.
 __device__ __forceinline__ float widen_lo(bf16_t, uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float widen_hi(bf16_t, uint32_t w) {
     return __uint_as_float(w & 0xffff0000u);
@@ -49,34 +50,39 @@ __device__ __forceinline__ float widen_hi(_Float16, uint32_t w) {
     return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(w >> 16)));
 }
 
+// The four corner values of one slice in load order: first element's pair,
+// second element's pair.
 template <typename TV>
-__device__ __forceinline__ float gather_p2(const uint2 *__restrict__ p2, const VolDims &d,
-                                           const Corner &k) {
-    const uint2 a = p2[k.base];
-    const uint2 b = p2[k.base + d.nxy];
-    const TV t{};
-    return blend(k, widen_lo(t, a.x), widen_hi(t, a.x), widen_lo(t, a.y), widen_hi(t, a.y),
-                 widen_lo(t, b.x), widen_hi(t, b.x), widen_lo(t, b.y), widen_hi(t, b.y));
+__device__ __forceinline__ f32x4_a8 load_pairs(const void *__restrict__ pk, long long e) {
+    if constexpr (sizeof(TV) == 4) {
+        return *reinterpret_cast<const f32x4_a8 *>(static_cast<const float2 *>(pk) + e);
+    } else {
+        const u32x2_a4 w =
+            *reinterpret_cast<const u32x2_a4 *>(static_cast<const uint32_t *>(pk) + e);
+        const TV t{};
+        f32x4_a8 r;
+        r.x = widen_lo(t, w.x);
+        r.y = widen_hi(t, w.x);
+        r.z = widen_lo(t, w.y);
+        r.w = widen_hi(t, w.y);
+        return r;
+    }
 }
 
-// The packed gather for the volume's storage type: float4 elements for FP32,
-// uint2 elements for 16-bit volumes.
-template <typename TV>
-__device__ __forceinline__ float gather_pk(const void *__restrict__ pk, const VolDims &d,
-                                           const Corner &k) {
-    if constexpr (sizeof(TV) == 4)
-        return gather_p4(static_cast<const float4 *>(pk), d, k);
-    else
-        return gather_p2<TV>(static_cast<const uint2 *>(pk), d, k);
+template <typename TV, bool TL>
+__device__ __forceinline__ float gather_pairs(const void *__restrict__ pk, const VolDims &d,
+                                              const Corner &k) {
+    const f32x4_a8 a = load_pairs<TV>(pk, k.base);
+    const f32x4_a8 b = load_pairs<TV>(pk, k.base + d.nxy);
+    return TL ? blend(k, a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w)
+              : blend(k, a.x, a.z, a.y, a.w, b.x, b.z, b.y, b.w);
 }
 
 // Value of the sample at fixed-point position (px, py, pz): its trilinear
 // lookup (0 for a warped sample outside the hull; in the ray-length mode, 1
-// inside and 0 outside).  TL: gather from the y-fastest copy; PK: from the
-// corner-packed copy `pk` (y-fastest when TL; element type by TV).
-template <typename TV, int MODE, bool WARP, bool TL, bool PK>
-__device__ __forceinline__ float sample_value(const TV *__restrict__ vol,
-                                              const void *__restrict__ pk, const VolDims &d,
+// inside and 0 outside).  TL: `pk` is the y-fastest copy.
+template <typename TV, int MODE, bool WARP, bool TL>
+__device__ __forceinline__ float sample_value(const void *__restrict__ pk, const VolDims &d,
                                               const WarpGrid &w, float tau, long long px,
                                               long long py, long long pz) {
     int ix, iy, iz;
@@ -84,17 +90,14 @@ __device__ __forceinline__ float sample_value(const TV *__restrict__ vol,
     const bool in = sample_corner<WARP>(d, w, tau, px, py, pz, ix, iy, iz, k.fx, k.fy, k.fz);
     if (MODE == FP_RECIP_ONES) return in ? 1.0f : 0.0f;
     k.base = TL ? base_t(d, ix, iy, iz) : base_x(d, ix, iy, iz);
-    const float v = PK   ? gather_pk<TV>(pk, d, k)
-                    : TL ? gather_t(vol, d, k)
-                         : gather(vol, d, k);
+    const float v = gather_pairs<TV, TL>(pk, d, k);
     return in ? v : 0.0f;
 }
 
 // One ray's projection value: the mean over sub-views of the step-weighted
 // trilinear samples, two samples per loop iteration (independent gathers).
-template <typename TV, int MODE, bool WARP, bool TL, bool PK>
+template <typename TV, int MODE, bool WARP, bool TL>
 __device__ __forceinline__ float march(const RayGrid &g, const WarpGrid &w,
-                                       const TV *__restrict__ vol,
                                        const void *__restrict__ pk, const VolDims &d,
                                        const TileCoord &t) {
     float y = 0.0f;
@@ -109,14 +112,14 @@ __device__ __forceinline__ float march(const RayGrid &g, const WarpGrid &w,
         long long px = r.qx, py = r.qy, pz = r.qz;
         int i = 0;
         for (; i + 1 < r.n; i += 2) {
-            acc0 += sample_value<TV, MODE, WARP, TL, PK>(vol, pk, d, w, tau, px, py, pz);
-            acc1 += sample_value<TV, MODE, WARP, TL, PK>(vol, pk, d, w, tau, px + r.tx,
-                                                         py + r.ty, pz + r.tz);
+            acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
+            acc1 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px + r.tx, py + r.ty,
+                                                     pz + r.tz);
             px += 2 * r.tx;
             py += 2 * r.ty;
             pz += 2 * r.tz;
         }
-        if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL, PK>(vol, pk, d, w, tau, px, py, pz);
+        if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
         y = fmaf(r.h, acc0 + acc1, y);
     }
     return y / static_cast<float>(g.n_sub);
@@ -289,7 +292,7 @@ __device__ float march_tube(const RayGrid &g, const float *__restrict__ vol, con
     return y / static_cast<float>(g.n_sub);
 }
 
-// Occupancy caps.  The rays gather from the corner-packed copies; with more
+// Occupancy caps.  The rays gather from the pair-packed copies; with more
 // concurrent rays than the caches hold their patches evict each other.
 // Measured at 512^3 x 720 x 768^2 (results bitwise identical): FP32 866 ms at
 // 5 waves per SIMD, 782 ms at 3, 876 ms at 2, 1066 ms at 8; 16-bit 823 ms at
@@ -332,25 +335,13 @@ void fp_kernel(RayGrid g, WarpGrid w,
         return;
     }
     // projections whose rays run mainly along x read the y-fastest copy
-    const TV *vt = static_cast<const TV *>(ex.vol_t);
     const double uc = static_cast<double>((t.iu & ~(TILE_U - 1)) + TILE_U / 2);
     const double vc = static_cast<double>((t.iv & ~(TILE_V - 1)) + TILE_V / 2);
     const bool xm = MODE != FP_RECIP_ONES && x_major(g.tab[t.p * g.n_sub], uc, vc);
-    // corner-packed copies of the volume's storage type
-    const void *pkx = sizeof(TV) == 4 ? static_cast<const void *>(ex.p4)
-                                      : static_cast<const void *>(ex.p2);
-    const void *pky = sizeof(TV) == 4 ? static_cast<const void *>(ex.p4t)
-                                      : static_cast<const void *>(ex.p2t);
-    const bool pk = MODE != FP_RECIP_ONES && pkx != nullptr;
     float y = 0.0f;
-    if (active) {
-        if (pk)
-            y = (xm && pky) ? march<TV, MODE, WARP, true, true>(g, w, vol, pky, d, t)
-                            : march<TV, MODE, WARP, false, true>(g, w, vol, pkx, d, t);
-        else
-            y = (xm && vt) ? march<TV, MODE, WARP, true, false>(g, w, vt, nullptr, d, t)
-                           : march<TV, MODE, WARP, false, false>(g, w, vol, nullptr, d, t);
-    }
+    if (active)
+        y = xm ? march<TV, MODE, WARP, true>(g, w, ex.py, d, t)
+               : march<TV, MODE, WARP, false>(g, w, ex.px, d, t);
     const int pix = (t.k * g.n_v + t.iv) * g.n_u + t.iu;
     if (MODE == FP_PLAIN) {
         if (active) st(out, pix, y);

@@ -124,81 +124,56 @@ __global__ __launch_bounds__(THREADS) void repack_warp_kernel(const float *U, fl
     if (i < n) out[i] = make_float4(U[3 * i], U[3 * i + 1], U[3 * i + 2], 0.0f);
 }
 
-// dst[z][x][y] = src[z][y][x] through 32 x 32 LDS tiles (reads and writes
-// coalesced); T is the storage word (4 or 2 bytes).
+// Pair-packed copies (FpExtra): px element (x, y, z) holds v(x, y), v(x, y+1),
+// x fastest; py element (y, x, z) holds v(x, y), v(x+1, y), y fastest (indices
+// clamped at the last row and column, whose second values the gathers never
+// read).  A block stages a 32 x 32 tile of one slice and its high-side border
+// in LDS and writes both copies from it, so the volume is read once and every
+// access is coalesced.  Bound by HBM: 4 bytes in, 16 out per FP32 voxel.
+template <typename T> struct PairOf;
+template <> struct PairOf<float> {
+    typedef float2 type;
+    static __device__ __forceinline__ float2 make(float a, float b) { return make_float2(a, b); }
+};
+template <> struct PairOf<uint16_t> {
+    typedef uint32_t type;
+    static __device__ __forceinline__ uint32_t make(uint16_t a, uint16_t b) {
+        return a | (static_cast<uint32_t>(b) << 16);
+    }
+};
+
 template <typename T>
-__global__ __launch_bounds__(256) void transpose_xy_kernel(const T *__restrict__ src,
-                                                           T *__restrict__ dst, int nx, int ny) {
-    __shared__ T tile[32][33];
-    const size_t plane = static_cast<size_t>(blockIdx.z) * nx * ny;
-    const int x0 = blockIdx.x * 32, y0 = blockIdx.y * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8
-    for (int j = ty; j < 32; j += 8) {
-        const int x = x0 + tx, y = y0 + j;
-        if (x < nx && y < ny) tile[j][tx] = src[plane + static_cast<size_t>(y) * nx + x];
-    }
-    __syncthreads();
-    for (int j = ty; j < 32; j += 8) {
-        const int y = y0 + tx, x = x0 + j;
-        if (x < nx && y < ny) dst[plane + static_cast<size_t>(x) * ny + y] = tile[tx][j];
-    }
-}
-
-// Corner-packed copies: element (x, y, z) holds v(x, y), v(x+1, y), v(x, y+1),
-// v(x+1, y+1) of slice z (indices clamped at the last row and column, whose
-// elements the gathers never read).  XF: x-fastest layout, else y-fastest.
-template <bool XF>
-__global__ __launch_bounds__(THREADS) void pack_corners_kernel(const float *__restrict__ v,
-                                                               float4 *__restrict__ out, int nx,
-                                                               int ny, size_t n) {
-    const size_t stride = static_cast<size_t>(gridDim.x) * THREADS;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * THREADS + threadIdx.x; i < n; i += stride) {
-        int x, y;
-        size_t z;
-        if (XF) {
-            x = static_cast<int>(i % nx);
-            const size_t r = i / nx;
-            y = static_cast<int>(r % ny);
-            z = r / ny;
-        } else {
-            y = static_cast<int>(i % ny);
-            const size_t r = i / ny;
-            x = static_cast<int>(r % nx);
-            z = r / nx;
+__global__ __launch_bounds__(THREADS) void pack_pairs_kernel(const T *__restrict__ v,
+                                                             typename PairOf<T>::type *__restrict__ px,
+                                                             typename PairOf<T>::type *__restrict__ py,
+                                                             int nx, int ny, int tiles_x,
+                                                             int tiles_y, unsigned tiles) {
+    __shared__ T tile[33][34];
+    const int c = threadIdx.x & 31, r = threadIdx.x >> 5;   // 32 x 8
+    for (unsigned t = blockIdx.x; t < tiles; t += gridDim.x) {
+        const unsigned q = t / tiles_x;
+        const int x0 = static_cast<int>(t - q * tiles_x) * 32;
+        const unsigned z = q / tiles_y;
+        const int y0 = static_cast<int>(q - z * tiles_y) * 32;
+        const size_t plane = static_cast<size_t>(z) * nx * ny;
+        if (t != blockIdx.x) __syncthreads();   // the previous tile's reads are done
+        for (int i = threadIdx.x; i < 33 * 33; i += THREADS) {
+            const int j = i / 33, k = i - j * 33;
+            const int x = min(x0 + k, nx - 1), y = min(y0 + j, ny - 1);
+            tile[j][k] = v[plane + static_cast<size_t>(y) * nx + x];
         }
-        const int x1 = min(x + 1, nx - 1), y1 = min(y + 1, ny - 1);
-        const float *s = v + z * nx * ny;
-        out[i] = make_float4(s[static_cast<size_t>(y) * nx + x], s[static_cast<size_t>(y) * nx + x1],
-                             s[static_cast<size_t>(y1) * nx + x], s[static_cast<size_t>(y1) * nx + x1]);
-    }
-}
-
-template <bool XF>
-__global__ __launch_bounds__(THREADS) void pack_corners16_kernel(const uint16_t *__restrict__ v,
-                                                                 uint2 *__restrict__ out, int nx,
-                                                                 int ny, size_t n) {
-    const size_t stride = static_cast<size_t>(gridDim.x) * THREADS;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * THREADS + threadIdx.x; i < n; i += stride) {
-        int x, y;
-        size_t z;
-        if (XF) {
-            x = static_cast<int>(i % nx);
-            const size_t r = i / nx;
-            y = static_cast<int>(r % ny);
-            z = r / ny;
-        } else {
-            y = static_cast<int>(i % ny);
-            const size_t r = i / ny;
-            x = static_cast<int>(r % nx);
-            z = r / nx;
+        __syncthreads();
+#pragma unroll
+        for (int j = r; j < 32; j += 8) {
+            const int x = x0 + c, y = y0 + j;
+            if (x < nx && y < ny)
+                px[plane + static_cast<size_t>(y) * nx + x] =
+                    PairOf<T>::make(tile[j][c], tile[j + 1][c]);
+            const int xt = x0 + j, yt = y0 + c;
+            if (xt < nx && yt < ny)
+                py[plane + static_cast<size_t>(xt) * ny + yt] =
+                    PairOf<T>::make(tile[c][j], tile[c][j + 1]);
         }
-        const int x1 = min(x + 1, nx - 1), y1 = min(y + 1, ny - 1);
-        const uint16_t *s = v + z * nx * ny;
-        const uint32_t c00 = s[static_cast<size_t>(y) * nx + x],
-                       c10 = s[static_cast<size_t>(y) * nx + x1];
-        const uint32_t c01 = s[static_cast<size_t>(y1) * nx + x],
-                       c11 = s[static_cast<size_t>(y1) * nx + x1];
-        out[i] = make_uint2(c00 | (c10 << 16), c01 | (c11 << 16));
     }
 }
 
@@ -229,42 +204,21 @@ hipError_t launch_pack_polar(const float *vol, float4 *p4, int nr, int nphi, int
     return hipGetLastError();
 }
 
-hipError_t launch_pack_corners(const float *vol, float4 *p4, float4 *p4t, int nx, int ny, int nz,
-                               hipStream_t s) {
-    const size_t n = static_cast<size_t>(nx) * ny * nz;
-    if (n == 0) return hipSuccess;
-    if (p4)
-        hipLaunchKernelGGL(pack_corners_kernel<true>, dim3(grid_for(n)), dim3(THREADS), 0, s, vol,
-                           p4, nx, ny, n);
-    if (p4t)
-        hipLaunchKernelGGL(pack_corners_kernel<false>, dim3(grid_for(n)), dim3(THREADS), 0, s,
-                           vol, p4t, nx, ny, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_pack_corners16(const uint16_t *vol, uint2 *p2, uint2 *p2t, int nx, int ny,
-                                 int nz, hipStream_t s) {
-    const size_t n = static_cast<size_t>(nx) * ny * nz;
-    if (n == 0) return hipSuccess;
-    if (p2)
-        hipLaunchKernelGGL(pack_corners16_kernel<true>, dim3(grid_for(n)), dim3(THREADS), 0, s,
-                           vol, p2, nx, ny, n);
-    if (p2t)
-        hipLaunchKernelGGL(pack_corners16_kernel<false>, dim3(grid_for(n)), dim3(THREADS), 0, s,
-                           vol, p2t, nx, ny, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_transpose_xy(const void *src, void *dst, int dtype, int nx, int ny, int nz,
-                               hipStream_t s) {
+hipError_t launch_pack_pairs(const void *vol, int dtype, void *px, void *py, int nx, int ny, int nz,
+                             hipStream_t s) {
     if (nx <= 0 || ny <= 0 || nz <= 0) return hipSuccess;
-    const dim3 grid((nx + 31) / 32, (ny + 31) / 32, nz), block(256);
+    const int tx = (nx + 31) / 32, ty = (ny + 31) / 32;
+    // fewer tiles than voxels, so below 2^31
+    const unsigned tiles = static_cast<unsigned>(tx) * static_cast<unsigned>(ty) * static_cast<unsigned>(nz);
+    const dim3 grid(tiles < (1u << 20) ? tiles : (1u << 20)), block(THREADS);
     if (dtype == F32)
-        hipLaunchKernelGGL(transpose_xy_kernel<uint32_t>, grid, block, 0, s,
-                           static_cast<const uint32_t *>(src), static_cast<uint32_t *>(dst), nx, ny);
+        hipLaunchKernelGGL(pack_pairs_kernel<float>, grid, block, 0, s,
+                           static_cast<const float *>(vol), static_cast<float2 *>(px),
+                           static_cast<float2 *>(py), nx, ny, tx, ty, tiles);
     else
-        hipLaunchKernelGGL(transpose_xy_kernel<uint16_t>, grid, block, 0, s,
-                           static_cast<const uint16_t *>(src), static_cast<uint16_t *>(dst), nx, ny);
+        hipLaunchKernelGGL(pack_pairs_kernel<uint16_t>, grid, block, 0, s,
+                           static_cast<const uint16_t *>(vol), static_cast<uint32_t *>(px),
+                           static_cast<uint32_t *>(py), nx, ny, tx, ty, tiles);
     return hipGetLastError();
 }
 
