@@ -38,6 +38,10 @@ struct RayGrid {
     // detector tiling of the launch
     int tiles_u, tiles_v;
     int total_blocks;    // tiles_u * tiles_v * n_views
+    // launch order: units of grp projections x run tiles (tile_coord), and
+    // the workgroups of the launch (whole units, a multiple of N_XCD)
+    int grp, run;
+    unsigned blocks;
     int tube = 0;        // forward projection of FP32 volumes through LDS-staged tubes
 };
 

@@ -252,10 +252,7 @@ __global__ __launch_bounds__(PROJ_THREADS) void count_cyl_kernel(RayGrid g, CylG
     if ((threadIdx.x & 63) == 0) atomicAdd(count, n);
 }
 
-inline dim3 cyl_grid(const RayGrid &g) {
-    const int per = (g.total_blocks + N_XCD - 1) / N_XCD;
-    return dim3(static_cast<unsigned>(per * N_XCD));
-}
+inline dim3 cyl_grid(const RayGrid &g) { return dim3(g.blocks); }
 
 template <typename TV, typename TS>
 hipError_t fp_cyl_mode(const RayGrid &g, const CylGrid &c, const void *vol, void *out, int mode,

@@ -1,11 +1,10 @@
 // Ray-driven forward projector and its exact-transpose backprojector (gfx950).
 //
 // One workgroup owns a 16x16 detector tile of one projection; each lane owns
-// one pixel ray.  The four wave64s of a workgroup take 8x8 quadrants so that
+// one pixel ray.  The four wave64s of a workgroup take 16x4 pixels so that
 // the 64 rays of a wave sample a compact patch of the volume at every step.
-// Workgroup ids are swizzled so that each XCD walks a contiguous run of
-// (tile, projection) pairs: consecutive projections of one tile revisit almost
-// the same voxels, which then stay in that XCD's L2.
+// Workgroup ids are mapped so that an XCD's concurrent workgroups are a few
+// consecutive projections of neighbouring tiles (tile_coord).
 //
 // Per ray (Sec. 4.1, projection operator; Sec. 2.2 geometry):
 //   FP64: direction M^-1 (u, v, 1), slab clip to the voxel-centre hull,
@@ -94,12 +93,98 @@ __device__ __forceinline__ float sample_value(const void *__restrict__ pk, const
     return in ? v : 0.0f;
 }
 
-// One ray's projection value: the mean over sub-views of the step-weighted
-// trilinear samples, two samples per loop iteration (independent gathers).
+// The same for a ray none of whose samples needs a corner clamp (p0, p1: the
+// copy at slices 0 and 1).
+template <typename TV, bool TL>
+__device__ __forceinline__ float clean_sample(const char *__restrict__ p0,
+                                              const char *__restrict__ p1, const VolDims &d,
+                                              long long px, long long py, long long pz) {
+    constexpr unsigned EB = sizeof(TV) == 4 ? 8 : 4;   // bytes of an element
+    int ix, iy, iz;
+    Corner k;
+    fx_split(px, ix, k.fx);
+    fx_split(py, iy, k.fy);
+    fx_split(pz, iz, k.fz);
+    // 24-bit product: sides are below 2^22
+    const unsigned row = TL ? __umul24(ix, d.ny) + iy : __umul24(iy, d.nx) + ix;
+    const unsigned base = static_cast<unsigned>(iz) * static_cast<unsigned>(d.nxy) + row;
+    const size_t off = static_cast<size_t>(base) * EB;
+    const f32x4_a8 a = load_pairs<TV>(p0 + off, 0);
+    const f32x4_a8 b = load_pairs<TV>(p1 + off, 0);
+    return TL ? blend(k, a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w)
+              : blend(k, a.x, a.z, a.y, a.w, b.x, b.z, b.y, b.w);
+}
+
+// Sum of a ray's samples, alternately into two accumulators.
 template <typename TV, int MODE, bool WARP, bool TL>
-__device__ __forceinline__ float march(const RayGrid &g, const WarpGrid &w,
-                                       const void *__restrict__ pk, const VolDims &d,
-                                       const TileCoord &t) {
+__device__ __forceinline__ float ray_sum(const VolDims &d, const WarpGrid &w, float tau,
+                                         const Ray &r, const void *__restrict__ pk) {
+    float acc0 = 0.0f, acc1 = 0.0f;
+    long long px = r.qx, py = r.qy, pz = r.qz;
+    int i = 0;
+    if constexpr (!WARP && MODE != FP_RECIP_ONES) {
+        // Positions are exactly linear in the sample index, so if the first
+        // and the last corner need no clamp, none does.  Only rays in a face
+        // of the hull fail this; a wave with one of them takes the loop below.
+        auto in = [](long long q, int n) {
+            return static_cast<unsigned>(static_cast<int>(q >> FX)) <= static_cast<unsigned>(n - 2);
+        };
+        const long long m = r.n - 1;
+        const bool clean = in(px, d.nx) && in(py, d.ny) && in(pz, d.nz) &&
+                           in(px + m * r.tx, d.nx) && in(py + m * r.ty, d.ny) &&
+                           in(pz + m * r.tz, d.nz);
+        if (__ballot(!clean) == 0) {
+            const char *p0 = static_cast<const char *>(pk);
+            const char *p1 = p0 + static_cast<size_t>(d.nxy) * (sizeof(TV) == 4 ? 8 : 4);
+            // four samples' gathers in flight
+            for (; i + 3 < r.n; i += 4) {
+                const long long x1 = px + r.tx, y1 = py + r.ty, z1 = pz + r.tz;
+                const long long x2 = x1 + r.tx, y2 = y1 + r.ty, z2 = z1 + r.tz;
+                const long long x3 = x2 + r.tx, y3 = y2 + r.ty, z3 = z2 + r.tz;
+                acc0 += clean_sample<TV, TL>(p0, p1, d, px, py, pz);
+                acc1 += clean_sample<TV, TL>(p0, p1, d, x1, y1, z1);
+                acc0 += clean_sample<TV, TL>(p0, p1, d, x2, y2, z2);
+                acc1 += clean_sample<TV, TL>(p0, p1, d, x3, y3, z3);
+                px = x3 + r.tx;
+                py = y3 + r.ty;
+                pz = z3 + r.tz;
+            }
+            for (; i < r.n; ++i) {
+                const float v = clean_sample<TV, TL>(p0, p1, d, px, py, pz);
+                if (i & 1)
+                    acc1 += v;
+                else
+                    acc0 += v;
+                px += r.tx;
+                py += r.ty;
+                pz += r.tz;
+            }
+            return acc0 + acc1;
+        }
+    }
+    for (; i + 1 < r.n; i += 2) {
+        acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
+        acc1 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px + r.tx, py + r.ty, pz + r.tz);
+        px += 2 * r.tx;
+        py += 2 * r.ty;
+        pz += 2 * r.tz;
+    }
+    if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
+    return acc0 + acc1;
+}
+
+// One ray's projection value: the mean over sub-views of the step-weighted
+// trilinear samples.  The samples of a wave at one index lie near one plane
+// parallel to the face its rays enter through (each ray starts half a step
+// inside it), so a wave whose rays mostly enter through an x face, where they
+// spread over y and z, reads the y-fastest copy, and one entering through a y
+// face the x-fastest copy: neighbouring lanes then share cache lines.  (The
+// copy was chosen by the rays' direction before; near the diagonals up to
+// half of the rays enter through the other face, and each lane then touched a
+// line of its own.)  The values do not depend on the choice.
+template <typename TV, int MODE, bool WARP>
+__device__ __forceinline__ float march(const RayGrid &g, const WarpGrid &w, const FpExtra &ex,
+                                       const VolDims &d, const TileCoord &t) {
     float y = 0.0f;
     for (int s = 0; s < g.n_sub; ++s) {
         const SubView &sv = g.tab[t.p * g.n_sub + s];
@@ -108,19 +193,16 @@ __device__ __forceinline__ float march(const RayGrid &g, const WarpGrid &w,
                        g.nz, g.step, r))
             continue;
         const float tau = static_cast<float>(sv.tau);
-        float acc0 = 0.0f, acc1 = 0.0f;
-        long long px = r.qx, py = r.qy, pz = r.qz;
-        int i = 0;
-        for (; i + 1 < r.n; i += 2) {
-            acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
-            acc1 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px + r.tx, py + r.ty,
-                                                     pz + r.tz);
-            px += 2 * r.tx;
-            py += 2 * r.ty;
-            pz += 2 * r.tz;
+        float sum;
+        if (MODE == FP_RECIP_ONES) {
+            sum = ray_sum<TV, MODE, WARP, false>(d, w, tau, r, nullptr);
+        } else {
+            const bool xe = r.axis == 0 || (r.axis == 2 && fabsf(r.fx) > fabsf(r.fy));
+            const bool yfast = 2 * __popcll(__ballot(xe)) > __popcll(__ballot(true));
+            sum = yfast ? ray_sum<TV, MODE, WARP, true>(d, w, tau, r, ex.py)
+                        : ray_sum<TV, MODE, WARP, false>(d, w, tau, r, ex.px);
         }
-        if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
-        y = fmaf(r.h, acc0 + acc1, y);
+        y = fmaf(r.h, sum, y);
     }
     return y / static_cast<float>(g.n_sub);
 }
@@ -292,18 +374,15 @@ __device__ float march_tube(const RayGrid &g, const float *__restrict__ vol, con
     return y / static_cast<float>(g.n_sub);
 }
 
-// Occupancy caps.  The rays gather from the pair-packed copies; with more
-// concurrent rays than the caches hold their patches evict each other.
-// Measured at 512^3 x 720 x 768^2 (results bitwise identical): FP32 866 ms at
-// 5 waves per SIMD, 782 ms at 3, 876 ms at 2, 1066 ms at 8; 16-bit 823 ms at
-// 8, 765 at 6, 711 at 5, 674 at 4, 689 at 3, 808 at 2.  The warped variants
-// keep the default: their 111 registers already limit them to 4 waves, and
-// capping them lower was slower (helical 256^3, 1200 x 4 sub-views of
-// 512 x 256, 32^3 warp: 700 ms at 4, 714 at 3, 777 at 2).  The ray-length
-// mode (no gathers) keeps the default too.
+// Occupancy caps: with more concurrent rays than the caches hold, their
+// patches evict each other.  SIRT step over 180 of 720 views of 768^2 at 512^3
+// (72 views for 16-bit storage), results bitwise identical: FP32 440.7 ms at 3
+// waves per SIMD, 442.6 at 2, 447.0 at 4; 16-bit 173.3 ms at 3, 173.9 at 4,
+// 175.6 at 5.  The warped variants keep the default (their registers limit
+// them to 4 waves), and so does the ray-length mode (no gathers).
 template <typename TV, int MODE, bool WARP>
 constexpr int fp_max_waves() {
-    return (WARP || MODE == FP_RECIP_ONES) ? 8 : (sizeof(TV) == 4 ? 3 : 4);
+    return (WARP || MODE == FP_RECIP_ONES) ? 8 : 3;
 }
 
 template <typename TV, typename TS, int MODE, bool WARP, bool TUBE = false>
@@ -334,14 +413,8 @@ void fp_kernel(RayGrid g, WarpGrid w,
         }
         return;
     }
-    // projections whose rays run mainly along x read the y-fastest copy
-    const double uc = static_cast<double>((t.iu & ~(TILE_U - 1)) + TILE_U / 2);
-    const double vc = static_cast<double>((t.iv & ~(TILE_V - 1)) + TILE_V / 2);
-    const bool xm = MODE != FP_RECIP_ONES && x_major(g.tab[t.p * g.n_sub], uc, vc);
     float y = 0.0f;
-    if (active)
-        y = xm ? march<TV, MODE, WARP, true>(g, w, ex.py, d, t)
-               : march<TV, MODE, WARP, false>(g, w, ex.px, d, t);
+    if (active) y = march<TV, MODE, WARP>(g, w, ex, d, t);
     const int pix = (t.k * g.n_v + t.iv) * g.n_u + t.iu;
     if (MODE == FP_PLAIN) {
         if (active) st(out, pix, y);
@@ -377,10 +450,7 @@ __global__ __launch_bounds__(PROJ_THREADS) void count_kernel(RayGrid g,
     if ((threadIdx.x & 63) == 0) atomicAdd(count, n);
 }
 
-inline dim3 proj_grid(const RayGrid &g) {
-    const int per = (g.total_blocks + N_XCD - 1) / N_XCD;
-    return dim3(static_cast<unsigned>(per * N_XCD));
-}
+inline dim3 proj_grid(const RayGrid &g) { return dim3(g.blocks); }
 
 // FP32 volumes without warp may take the LDS-staged tube gather.
 template <typename TV, typename TS, int M, bool W>
