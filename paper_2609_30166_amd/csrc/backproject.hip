@@ -30,6 +30,7 @@
 
 #include "ray_common.h"
 
+#include <climits>
 #include <type_traits>
 
 namespace ctrex {
@@ -62,20 +63,24 @@ static_assert(LDS_SZ % 16 == 3, "plane stride");
 // Owner-computes bricks (the default form): a brick takes exactly the
 // samples whose lower corner lies in it, so every sample is walked once and
 // issues its eight atomics once, into LDS cells for the brick's voxels plus
-// one halo layer on the high side of each axis (33 x 17 x 17 cells, 76.3 KB;
-// row and plane strides 1 mod 16).  Every brick then adds its cells, halo
-// included, into a 64-bit integer volume with global atomics; integer sums
-// are exact, so neighbours' halos and projection chunks combine in any order
-// and the result stays bitwise reproducible.  All workgroups use one
-// fixed-point scale for that.  The direct form above (a sample walked by every
-// brick it touches, each brick writing only its own voxels) needs no
-// volume-sized buffer and serves the allocation-free entry point.
+// one halo layer on the high side of each axis (33 x 17 x 17 cells).  Row and
+// plane strides are 2 and 7 (mod 16): a wave's samples lie near a plane
+// parallel to a hull face, and with both 1 (mod 16) the cells along each
+// diagonal of that patch shared a bank (SIRT step over 180 views of 768^2 at
+// 512^3: 390 ms; 371 ms with 2 and 7, 371 to 374 ms with five other pairs).
+// Every brick then adds its cells, halo included, into a 64-bit integer volume
+// with global atomics; integer sums are exact, so neighbours' halos and
+// projection chunks combine in any order and the result stays bitwise
+// reproducible.  All workgroups use one fixed-point scale for that.  The
+// direct form above (a sample walked by every brick it touches, each brick
+// writing only its own voxels) needs no volume-sized buffer and serves the
+// allocation-free entry point.
 constexpr int OWN_X = 32, OWN_Y = 16, OWN_Z = 16;
-constexpr int OWN_SY = OWN_X + 1;
-constexpr int OWN_SZ = OWN_SY * (OWN_Y + 1);
+constexpr int OWN_SY = OWN_X + 2;
+constexpr int OWN_SZ = OWN_SY * (OWN_Y + 1) + 5;
 constexpr int OWN_CELLS = OWN_SZ * (OWN_Z + 1);
 constexpr int MAX_CELLS = OWN_CELLS > LDS_CELLS ? OWN_CELLS : LDS_CELLS;
-static_assert(OWN_SY % 16 == 1 && OWN_SZ % 16 == 1, "owner strides");
+static_assert(OWN_SY % 16 == 2 && OWN_SZ % 16 == 7, "owner strides");
 
 struct BrickGrid {
     int bx, by, bz;       // brick size (voxels), at most BRICK_X x BRICK_Y x BRICK_Z
@@ -633,7 +638,7 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
         for (int i = threadIdx.x; i < OWN_CELLS; i += BP_THREADS) {
             const int lz = i / OWN_SZ;
             const int rem = i - lz * OWN_SZ;
-            const int ly = rem / OWN_SY;
+            const int ly = rem / OWN_SY;   // OWN_Y + 1 in a plane's padding
             const int lx = rem - ly * OWN_SY;
             const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
             const unsigned long long q = acc[i];
@@ -662,6 +667,344 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
         } else {
             *dst = v;
         }
+    }
+}
+
+// The unwarped owner form (the default backprojector).  One 16-wave workgroup
+// per CU (its LDS brick and its waves' ray tables take 141 KB of the 160).
+//
+// Work is handed out in 8x8 pixel blocks: per batch of 64 (projection,
+// sub-view) pairs, one wave projects the brick onto each pair's detector and
+// prefix-sums the pairs' block counts, and the 16 waves take blocks from an
+// LDS counter.  (A wave per pair left 7 of 16 waves idle in a 9-projection
+// subset and 12 of 16 in a 4-projection chunk.)  Integer sums do not depend on
+// the order, so the result stays bitwise reproducible.
+//
+// Bound by the LDS atomics (6.4 cycles of a CU each at least, 9 with their
+// conflicts) and by VALU issue, so the sample loop is kept short: positions
+// are relative to the brick; each ray's range holds exactly the samples whose
+// lower corner the brick owns (trimmed with the exact positions in the
+// set-up), so the loop tests nothing; the merged sums are cleared where they
+// are flushed; one instruction rounds and converts.  Against a wave per pair
+// with an ownership test, selects and separate rounding per sample, 180 views
+// of 768^2 at 512^3 took 258 ms instead of 324, 9 views of 384^2 at 256^3
+// 1.8 ms instead of 3.0.
+constexpr int OWN_BATCH = 64;
+
+// floor(c + 1/2) for |c| < 2^31: the nearest integer.
+__device__ __forceinline__ unsigned long long to_fixed_near(float c) {
+    int i;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(i) : "v"(c));
+    return static_cast<unsigned long long>(static_cast<long long>(i));
+}
+
+template <typename TS, int MODE>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void bp_own_kernel(
+    RayGrid g, const double *__restrict__ Pmat, const TS *__restrict__ sino,
+    const float *__restrict__ rmax, BrickGrid bg) {
+    constexpr int NT = 1024;
+    __shared__ unsigned long long acc[OWN_CELLS];
+    __shared__ RayRec rays[NT];
+    __shared__ int4 box[OWN_BATCH];        // u0, v0, blocks per row, u1 - u0
+    __shared__ int box_v1[OWN_BATCH];
+    __shared__ int blk_end[OWN_BATCH];     // inclusive prefix of the block counts
+    __shared__ int next_item;
+    RayRec *const tabw = rays + (threadIdx.x & ~63);
+    const int lane = threadIdx.x & 63;
+    // ---- block -> (brick, projection chunk): rows of bricks go to the XCDs
+    // in turn, so that they stay equally loaded where the ends of the volume
+    // see few rays
+    const int per_row = bg.nbx * bg.chunks;
+    const int j = blockIdx.x / N_XCD, jr = j / per_row;
+    const int row = jr * N_XCD + blockIdx.x % N_XCD;
+    if (row >= bg.nby * bg.nbz) return;
+    const int jx = j - jr * per_row;
+    const int ibx = jx / bg.chunks, chunk = jx - ibx * bg.chunks;
+    const int ibz = row / bg.nby, iby = row - ibz * bg.nby;
+    const int x0 = ibx * bg.bx, y0 = iby * bg.by, z0 = ibz * bg.bz;
+    const int ex = min(bg.bx, g.nx - x0), ey = min(bg.by, g.ny - y0), ez = min(bg.bz, g.nz - z0);
+    const double cmax =
+        contribution_bound(g, (MODE == BP_ONES) ? 1.0 : static_cast<double>(*rmax), bg.wscale);
+    // nothing to add, or NaN / Inf in the input (the finishing pass writes
+    // NaN then), or a brick past the last lower corner n - 2
+    if (!(cmax > 0.0 && cmax < __builtin_inf()) || x0 > g.nx - 2 || y0 > g.ny - 2 || z0 > g.nz - 2)
+        return;
+    for (int i = threadIdx.x; i < OWN_CELLS; i += NT) acc[i] = 0ull;
+    const double scale = uni(ldexp(1.0, uni(own_kexp(cmax, g, bg.cube_samples))));
+    const double off[3] = {0.5 * (g.nx - 1), 0.5 * (g.ny - 1), 0.5 * (g.nz - 1)};
+    // 1 / n_sub and the caller's factor (1 unless scaled; exact when a power of 2)
+    const float inv_sub = uni(bg.wscale / static_cast<float>(g.n_sub));
+    // largest side times 2^-22: four times the FP32 rounding error of a
+    // coordinate of a ray's start (the ray-range estimate is widened by it)
+    const float tol = uni(static_cast<float>(max(g.nx, max(g.ny, g.nz))) * 2.38418579e-7f);
+    const float lo[3] = {uni(x0 - tol), uni(y0 - tol), uni(z0 - tol)};
+    const float hi[3] = {uni(static_cast<float>(x0 + ex) + tol),
+                         uni(static_cast<float>(y0 + ey) + tol),
+                         uni(static_cast<float>(z0 + ez) + tol)};
+    // owned lower corners, relative to the brick: [0, e) on every axis, open
+    // towards the faces, where the clamp moves corners into the brick
+    const int mx = g.nx - 2 - x0, my = g.ny - 2 - y0, mz = g.nz - 2 - z0;
+    const int ax = x0 == 0 ? INT_MIN : 0, bx = mx < ex ? INT_MAX : ex - 1;
+    const int ay = y0 == 0 ? INT_MIN : 0, by = my < ey ? INT_MAX : ey - 1;
+    const int az = z0 == 0 ? INT_MIN : 0, bz = mz < ez ? INT_MAX : ez - 1;
+    // no clamp can act where the brick holds neither the first lower corner
+    // nor the last
+    const bool interior = x0 >= 1 && mx >= ex && y0 >= 1 && my >= ey && z0 >= 1 && mz >= ez;
+    const int k_first = chunk * bg.views_per_chunk;
+    const int n_pairs = (min(k_first + bg.views_per_chunk, g.n_views) - k_first) * g.n_sub;
+
+    for (int q0 = 0; q0 < n_pairs; q0 += OWN_BATCH) {
+        __syncthreads();   // the cells are cleared; the previous batch is done
+        if (threadIdx.x < OWN_BATCH) {
+            int nblk = 0;
+            const int q = q0 + threadIdx.x;
+            if (q < n_pairs) {
+                const int k = k_first + q / g.n_sub;
+                const int p = g.views ? g.views[k] : k;
+                const int sv_idx = p * g.n_sub + q % g.n_sub;
+                const double plo[3] = {lo[0], lo[1], lo[2]}, phi[3] = {hi[0], hi[1], hi[2]};
+                int u0 = 0, u1 = g.n_u - 1, v0 = 0, v1 = g.n_v - 1;
+                if (!project_box(Pmat + 12 * static_cast<size_t>(sv_idx), plo, phi, off, g.n_u,
+                                 g.n_v, u0, u1, v0, v1)) {
+                    u0 = v0 = 0;
+                    u1 = g.n_u - 1;
+                    v1 = g.n_v - 1;
+                }
+                const int bu = (u1 - u0 + 8) >> 3;
+                if (u0 <= u1 && v0 <= v1) nblk = bu * ((v1 - v0 + 8) >> 3);
+                box[threadIdx.x] = make_int4(u0, v0, bu, u1);
+                box_v1[threadIdx.x] = v1;
+            }
+            blk_end[threadIdx.x] = wave_inclusive_sum(nblk);
+            if (threadIdx.x == 0) next_item = 0;
+        }
+        __syncthreads();
+        const int items = uni(blk_end[OWN_BATCH - 1]);
+        const int my_end = blk_end[lane];
+        for (;;) {
+            int item = 0;
+            if (lane == 0) item = atomicAdd(&next_item, 1);
+            item = uni(item);
+            if (item >= items) break;
+            // the pair: the first whose prefix passes the item
+            const int qb = __popcll(__ballot(my_end <= item));
+            const int first = qb > 0 ? __builtin_amdgcn_readlane(my_end, qb - 1) : 0;
+            const int blk = item - first;
+            const int4 bxq = box[qb];
+            const int u0 = uni(bxq.x), v0 = uni(bxq.y), bu = uni(bxq.z), u1 = uni(bxq.w);
+            const int v1 = uni(box_v1[qb]);
+            const int q = q0 + qb;
+            const int kq = q / g.n_sub;
+            const int k = k_first + kq;
+            const int p = uni(g.views ? g.views[k] : k);
+            const SubView &sv = g.tab[p * g.n_sub + (q - kq * g.n_sub)];
+            const int bv = blk / bu;
+            const int iv = v0 + bv * 8 + (lane >> 3);
+            const int iu = u0 + (blk - bv * bu) * 8 + (lane & 7);
+            // ---- this lane's ray: the samples the brick owns
+            int len = 0, ib = 0;
+            float wq = 0.0f;   // h r / n_sub in fixed-point units
+            Ray r;
+            r.qx = r.qy = r.qz = r.tx = r.ty = r.tz = 0;
+            const float rv = (iu > u1 || iv > v1) ? 0.0f
+                             : (MODE == BP_ONES) ? 1.0f
+                                                 : ld(sino, (k * g.n_v + iv) * g.n_u + iu);
+            if (rv != 0.0f && setup_ray(sv, static_cast<double>(iu), static_cast<double>(iv), g.nx,
+                                        g.ny, g.nz, g.step, r)) {
+                // sample indices i with b + i s inside [lo, hi] on every axis,
+                // in FP32: a superset of the owned ones.  The FP32 start and
+                // step put b + i s within 2.8 2^-24 max side of the
+                // fixed-point position of sample i, and [lo, hi] is widened
+                // by 4 2^-24 max side; the index estimate itself is a
+                // reciprocal to 1 ulp and two roundings, under 4 2^-24 |t|,
+                // inside the margin of 1/64 + 2^-20 |t| samples.  An axis the ray does not move
+                // along (|s| under 1e-30: its samples drift by less than tol)
+                // only decides whether the ray hits.
+                float kmin = 0.0f, kmax = static_cast<float>(r.n - 1);
+                const float bv3[3] = {r.bx, r.by, r.bz};
+                const float sv3[3] = {r.fx, r.fy, r.fz};
+                bool hit = true;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const bool flat = fabsf(sv3[a]) < 1e-30f;
+                    const float inv = __builtin_amdgcn_rcpf(flat ? 1.0f : sv3[a]);
+                    const float t1 = (lo[a] - bv3[a]) * inv, t2 = (hi[a] - bv3[a]) * inv;
+                    const float tl = fminf(t1, t2), th = fmaxf(t1, t2);
+                    const float ml = fmaf(fabsf(tl), 9.5367431640625e-7f, 0.015625f);
+                    const float mh = fmaf(fabsf(th), 9.5367431640625e-7f, 0.015625f);
+                    kmin = flat ? kmin : fmaxf(kmin, tl - ml);
+                    kmax = flat ? kmax : fminf(kmax, th + mh);
+                    hit &= !(flat & ((bv3[a] < lo[a]) | (bv3[a] > hi[a])));
+                }
+                // positions relative to the brick
+                r.qx -= static_cast<long long>(x0) << FX;
+                r.qy -= static_cast<long long>(y0) << FX;
+                r.qz -= static_cast<long long>(z0) << FX;
+                if (hit && kmin <= kmax) {
+                    ib = max(static_cast<int>(ceilf(kmin)), 0);
+                    int ie = min(static_cast<int>(floorf(kmax)), r.n - 1);
+                    // the owned samples are a run (each coordinate is linear
+                    // in the index): trim the superset's ends to it
+                    auto owned = [&](int i) {
+                        const int kx = static_cast<int>((r.qx + i * r.tx) >> FX);
+                        const int ky = static_cast<int>((r.qy + i * r.ty) >> FX);
+                        const int kz = static_cast<int>((r.qz + i * r.tz) >> FX);
+                        return kx >= ax && kx <= bx && ky >= ay && ky <= by && kz >= az && kz <= bz;
+                    };
+                    while (ib <= ie && !owned(ib)) ++ib;
+                    while (ib <= ie && !owned(ie)) --ie;
+                    len = max(ie - ib + 1, 0);
+                    wq = static_cast<float>(static_cast<double>(r.h * rv * inv_sub) * scale);
+                }
+            }
+            // ---- exclusive prefix of the segment lengths over the wave
+            const int incl = wave_inclusive_sum(len);
+            const int S = incl - len;
+            const int T = __builtin_amdgcn_readlane(incl, 63);
+            if (T == 0) continue;   // uniform over the wave
+            const unsigned long long live = __ballot(len > 0);
+            {
+                // this lane's ray for the lanes that walk into it
+                const unsigned long long later = lane < 63 ? (live & (~0ull << (lane + 1))) : 0ull;
+                RayRec mine;
+                mine.px = r.qx + static_cast<long long>(ib) * r.tx;
+                mine.py = r.qy + static_cast<long long>(ib) * r.ty;
+                mine.pz = r.qz + static_cast<long long>(ib) * r.tz;
+                mine.tx = r.tx;
+                mine.ty = r.ty;
+                mine.tz = r.tz;
+                mine.wq = wq;
+                mine.end = incl;
+                mine.next = later ? __ffsll(static_cast<long long>(later)) - 1 : lane;
+                mine.pad = 0;
+                wave_sync();   // the previous block's reads of the table are done
+                tabw[lane] = mine;
+                wave_sync();
+            }
+            // ---- lane takes samples [start, end) of the wave's T
+            const int start = (T * lane) >> 6, end = (T * (lane + 1)) >> 6;
+            int jr0 = 0;   // last ray with S_j <= start: it owns sample `start`
+#pragma unroll
+            for (int st = 32; st > 0; st >>= 1) {
+                const int t = jr0 + st;
+                if (__shfl(S, t, 64) <= start) jr0 = t;
+            }
+            // the lane's first ray may be entered mid-way: `start - S_j`
+            // samples after its first sample in the brick
+            const long long m = start - __shfl(S, jr0, 64);
+            RayRec c = tabw[jr0];
+            c.px += m * c.tx;
+            c.py += m * c.ty;
+            c.pz += m * c.tz;
+            int pos = start;
+            // Each lane keeps the eight corner sums of the cell its last
+            // samples fell in and adds them to LDS when the next sample falls
+            // in another cell (consecutive samples, half a voxel apart, often
+            // share one) or could take a sum past a 32-bit integer.
+            auto walk = [&](auto clamp_tag) {
+                constexpr bool CLAMP = decltype(clamp_tag)::value;
+                auto corner = [&](int &lx, int &ly, int &lz, float &fx, float &fy, float &fz) {
+                    fx_split(c.px, lx, fx);
+                    fx_split(c.py, ly, fy);
+                    fx_split(c.pz, lz, fz);
+                    if (CLAMP) {
+                        auto clamp = [](int &l, float &f, int first, int last) {
+                            if (l < first) {
+                                l = first;
+                                f = 0.0f;
+                            }
+                            if (l > last) {
+                                l = last;
+                                f = 1.0f;
+                            }
+                        };
+                        clamp(lx, fx, -x0, mx);
+                        clamp(ly, fy, -y0, my);
+                        clamp(lz, fz, -z0, mz);
+                    }
+                    return __mul24(lz, OWN_SZ) + (__mul24(ly, OWN_SY) + lx);
+                };
+                int mcell;   // the first sample's cell
+                {
+                    int lx, ly, lz;
+                    float fx, fy, fz;
+                    mcell = corner(lx, ly, lz, fx, fy, fz);
+                }
+                float msum = 0.0f;
+                float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
+                float m4 = 0.0f, m5 = 0.0f, m6 = 0.0f, m7 = 0.0f;
+                auto flush = [&]() {
+                    unsigned long long *const f0 = acc + mcell;
+                    unsigned long long *const f1 = f0 + OWN_SZ;
+                    atomicAdd(f0, to_fixed_near(m0));
+                    atomicAdd(f0 + 1, to_fixed_near(m1));
+                    atomicAdd(f0 + OWN_SY, to_fixed_near(m2));
+                    atomicAdd(f0 + OWN_SY + 1, to_fixed_near(m3));
+                    atomicAdd(f1, to_fixed_near(m4));
+                    atomicAdd(f1 + 1, to_fixed_near(m5));
+                    atomicAdd(f1 + OWN_SY, to_fixed_near(m6));
+                    atomicAdd(f1 + OWN_SY + 1, to_fixed_near(m7));
+                };
+                auto sample = [&]() {
+                    if (pos == c.end) c = tabw[c.next];   // enter the next ray
+                    ++pos;
+                    int lx, ly, lz;
+                    float fx, fy, fz;
+                    const int cell = corner(lx, ly, lz, fx, fy, fz);
+                    c.px += c.tx;
+                    c.py += c.ty;
+                    c.pz += c.tz;
+                    const float aw = fabsf(c.wq);
+                    msum += aw;
+                    if (!(cell == mcell && msum <= OWN_MERGE_LIMIT)) {
+                        flush();
+                        m0 = m1 = m2 = m3 = m4 = m5 = m6 = m7 = 0.0f;
+                        msum = aw;
+                        mcell = cell;
+                    }
+                    const float gx0 = 1.0f - fx;
+                    const float gz1 = fz * c.wq, gz0 = c.wq - gz1;
+                    const float w01 = gz0 * fy, w00 = gz0 - w01, w11 = gz1 * fy, w10 = gz1 - w11;
+                    m0 = fmaf(w00, gx0, m0);
+                    m1 = fmaf(w00, fx, m1);
+                    m2 = fmaf(w01, gx0, m2);
+                    m3 = fmaf(w01, fx, m3);
+                    m4 = fmaf(w10, gx0, m4);
+                    m5 = fmaf(w10, fx, m5);
+                    m6 = fmaf(w11, gx0, m6);
+                    m7 = fmaf(w11, fx, m7);
+                };
+                // every lane has T / 64 samples, some one more; a run of
+                // merges ends after OWN_MERGE_MAX
+                for (int left = T >> 6; left > 0; left -= OWN_MERGE_MAX) {
+                    const int cnt = min(left, OWN_MERGE_MAX);
+                    for (int it = 0; it < cnt; ++it) sample();
+                    if (left > OWN_MERGE_MAX) {
+                        flush();
+                        m0 = m1 = m2 = m3 = m4 = m5 = m6 = m7 = 0.0f;
+                        msum = 0.0f;
+                    }
+                }
+                if (pos < end) sample();
+                if (start < end) flush();
+            };
+            if (interior)
+                walk(std::false_type{});
+            else
+                walk(std::true_type{});
+        }
+    }
+    __syncthreads();
+    // ---- add the brick's cells, halo included, into the integer volume
+    for (int i = threadIdx.x; i < OWN_CELLS; i += NT) {
+        const int lz = i / OWN_SZ;
+        const int rem = i - lz * OWN_SZ;
+        const int ly = rem / OWN_SY;
+        const int lx = rem - ly * OWN_SY;
+        const int gx = x0 + lx, gy = y0 + ly, gz = z0 + lz;
+        const unsigned long long q = acc[i];
+        if (q != 0ull && lx <= ex && ly <= ey && lz <= ez && gx < g.nx && gy < g.ny && gz < g.nz)
+            atomicAdd(bg.acc64 + (static_cast<size_t>(gz) * g.ny + gy) * g.nx + gx, q);
     }
 }
 
@@ -756,6 +1099,9 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
     const bool wp = w.U != nullptr;
     const dim3 grid(static_cast<unsigned>(per * N_XCD));
     const dim3 block(static_cast<unsigned>(wp ? bp_threads<true>() : bp_threads<false>()));
+    // unwarped owner form: whole rows of bricks, a multiple of N_XCD rows
+    const int rows = (bg.nby * bg.nbz + N_XCD - 1) / N_XCD * N_XCD;
+    const dim3 own_grid(static_cast<unsigned>(rows) * bg.nbx * bg.chunks);
     const size_t shmem = 0;   // the brick is static LDS
     size_t fblocks = (nvol + 255) / 256;
     if (fblocks > 65536) fblocks = 65536;
@@ -795,8 +1141,8 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
                 hipLaunchKernelGGL((bp_brick_kernel<T, M, true, true>), grid, block, shmem,     \
                                    stream, g, w, Pmat, SP, RM, vol, bg);                        \
             else                                                                                \
-                hipLaunchKernelGGL((bp_brick_kernel<T, M, false, true>), grid, block, shmem,    \
-                                   stream, g, w, Pmat, SP, RM, vol, bg);                        \
+                hipLaunchKernelGGL((bp_own_kernel<T, M>), own_grid, block, 0, stream, g, Pmat,  \
+                                   SP, RM, bg);                                                 \
         }                                                                                       \
         return finish(M);                                                                       \
     }
