@@ -288,10 +288,12 @@ ProjScratch proj_scratch(const ctrex_ctx *c, int32_t n_views) {
     return l;
 }
 
-// The cylindrical domain's calls: the correction volume, then the
-// corner-packed copy of the polar volume (16 bytes per voxel).
+// The cylindrical domain's calls: 20 bytes per voxel for the pair-packed
+// copies of the polar volume (8 per voxel, and 8 per voxel and ring of n_phi +
+// 1 angles).  The correction volume z lies under them: it is written and used
+// after a projection and before the next one's copies.
 struct CylScratch {
-    size_t z, packed, total;
+    size_t z, px, py, total;
 };
 
 // Write the copies of `vol` the rays gather from into `dst` (the shared
@@ -311,9 +313,24 @@ CylScratch cyl_scratch(const ctrex_ctx *c) {
     const size_t vox = static_cast<size_t>(c->cyl_nr) * c->cyl_nphi * c->cyl_nz;
     CylScratch l;
     l.z = 0;
-    l.packed = align_up(4 * vox);
-    l.total = align_up(l.packed + sizeof(float4) * vox);
+    l.px = 0;
+    l.py = align_up(8 * vox);
+    const size_t end = l.py + sizeof(float2) * static_cast<size_t>(c->cyl_nr) * (c->cyl_nphi + 1) *
+                                  c->cyl_nz;
+    l.total = align_up(std::max(align_up(4 * vox) + 16 * vox, end));
     return l;
+}
+
+// The same for a polar FP32 volume.
+int make_polar_copies(ctrex_ctx *c, const float *vol, void *scratch, FpExtra &ex, hipStream_t s) {
+    const CylScratch l = cyl_scratch(c);
+    char *sc = static_cast<char *>(scratch);
+    CTREX_HIP(c, launch_pack_polar(vol, reinterpret_cast<float2 *>(sc + l.px),
+                                   reinterpret_cast<float2 *>(sc + l.py), c->cyl_nr, c->cyl_nphi,
+                                   c->cyl_nz, s));
+    ex.px = sc + l.px;
+    ex.py = sc + l.py;
+    return CTREX_OK;
 }
 
 // ---------------------------------------------- allocation-free backprojection --
@@ -1240,10 +1257,7 @@ int ctrex_forward_project_cyl(ctrex_ctx *c, const void *vol, int32_t vol_dtype, 
         const CylScratch CL = cyl_scratch(c);
         void *scr;
         if ((st = ctx_scratch(c, CL.total, &scr))) return st;
-        float4 *pk = reinterpret_cast<float4 *>(static_cast<char *>(scr) + CL.packed);
-        CTREX_HIP(c, launch_pack_polar(static_cast<const float *>(vol), pk, c->cyl_nr, c->cyl_nphi,
-                                       c->cyl_nz, s));
-        ex.p4 = pk;
+        if ((st = make_polar_copies(c, static_cast<const float *>(vol), scr, ex, s))) return st;
     }
     CTREX_HIP(c, launch_forward_cyl(make_grid_cyl(c, dv, nv), cyl_of(c), vol, vol_dtype, sino,
                                     sino_dtype, FP_PLAIN, ex, s));
@@ -1337,7 +1351,7 @@ int ctrex_sirt_iterate_cyl(ctrex_ctx *c, float *vol, const void *sino, int32_t s
     double *partials = reinterpret_cast<double *>(ws + L.partials);
     double *resid = reinterpret_cast<double *>(ws + L.resid);
     const size_t vox = static_cast<size_t>(c->cyl_nr) * c->cyl_nphi * c->cyl_nz;
-    // scratch: the correction volume z, then the corner-packed copy
+    // scratch: the correction volume z, then the pair-packed copy
     const CylScratch CL = cyl_scratch(c);
     void *scr;
     if ((st = ctx_scratch(c, CL.total, &scr)) != CTREX_OK) return st;
@@ -1374,12 +1388,11 @@ int ctrex_sirt_iterate_cyl(ctrex_ctx *c, float *vol, const void *sino, int32_t s
     std::vector<double> host_norms;
     if (resid_norms) host_norms.reserve(n_iter);
     FpExtra ex{sino, Rw, partials};
-    float4 *p4 = reinterpret_cast<float4 *>(static_cast<char *>(scr) + CL.packed);
-    ex.p4 = p4;
+
     for (int32_t k = 0; k < n_iter; ++k) {
         PhaseTimer t_fp{c, s, nullptr, 0}, t_bp{c, s, nullptr, 1}, t_up{c, s, nullptr, 2};
         CTREX_HIP(c, t_fp.begin());
-        CTREX_HIP(c, launch_pack_polar(vol, p4, c->cyl_nr, c->cyl_nphi, c->cyl_nz, s));
+        if ((st = make_polar_copies(c, vol, scr, ex, s)) != CTREX_OK) return st;
         CTREX_HIP(c, launch_forward_cyl(g, cg, vol, F32, r, sino_dtype, FP_CORRECT, ex, s));
         CTREX_HIP(c, t_fp.end());
         CTREX_HIP(c, launch_sum_partials(partials, g.total_blocks, resid + (k % kResidCap), s));

@@ -73,11 +73,10 @@ struct FpExtra {
     // values, so a 16-byte (FP32) or 8-byte (16-bit) load of two consecutive
     // elements gives the four corners of a slice.  px: x-fastest
     // [nz][ny][nx], element (x, y, z) = v(x, y), v(x, y+1); py: y-fastest
-    // [nz][nx][ny], element (y, x, z) = v(x, y), v(x+1, y)
+    // [nz][nx][ny], element (y, x, z) = v(x, y), v(x+1, y).  Cylindrical
+    // domain: those of an FP32 polar volume (launch_pack_polar)
     const void *px = nullptr;
     const void *py = nullptr;
-    // cylindrical domain: corner-packed copy of an FP32 polar volume
-    const float4 *p4 = nullptr;
 };
 
 // Backprojection modes.
@@ -123,7 +122,8 @@ hipError_t launch_back_voxel(const RayGrid &g, const double *Pmat, const void *s
 // source and R_p M^-1 in that frame.
 struct CylGrid {
     int nr, nphi, nz;
-    float inv_dr, inv_dz, half_z, phi_scale;  // 1/dr, 1/dz, (nz-1)/2, nphi/(2 pi)
+    float inv_dr, inv_dz, half_z, phi_scale2;  // 1/dr, 1/dz, (nz-1)/2, nphi/pi
+    float full, half, quarter;                 // nphi and its fractions
     double rh2, hz;                           // hull radius^2 and half height
 };
 CylGrid make_cyl_grid(int nr, int nphi, int nz, double dr, double dz);
@@ -143,9 +143,11 @@ hipError_t launch_update(float *x, const float *z, const float *C, const float *
 // px / py = the pair-packed copies of FpExtra of a volume of storage type dtype.
 hipError_t launch_pack_pairs(const void *vol, int dtype, void *px, void *py, int nx, int ny, int nz,
                              hipStream_t s);
-// Corner-packed copy of a polar volume [nz][nphi][nr]: element (k, j, a) holds
-// v(a, j), v(a+1, j), v(a, j+1), v(a+1, j+1) of slice k, the angle periodic.
-hipError_t launch_pack_polar(const float *vol, float4 *p4, int nr, int nphi, int nz,
+// Pair-packed copies of a polar volume [nz][nphi][nr], the angle periodic:
+// px [nz][nphi][nr], element (k, j, a) = v(a, j), v(a, j+1); py
+// [nz][nr][nphi + 1], element (k, a, j) = v(a, j), v(a+1, j), the last of a
+// row repeating its first.
+hipError_t launch_pack_polar(const float *vol, float2 *px, float2 *py, int nr, int nphi, int nz,
                              hipStream_t s);
 hipError_t launch_convert(const void *src, int src_dtype, void *dst, int dst_dtype, size_t n,
                           hipStream_t stream);

@@ -11,7 +11,7 @@
 // sample, in FP32: r = |(x, y)|, phi = atan2(y, x), continuous indices
 // a = r / dr - 1/2 (clamped to [0, n_r - 1]: the core takes ring 0's values),
 // b = phi n_phi / (2 pi) (periodic), c = z / dz + (n_z - 1) / 2, trilinear
-// lookup (radial neighbours are one 8-byte load for FP32 volumes).  Sub-views
+// lookup (FP32 volumes: two 16-byte loads from a pair-packed copy).  Sub-views
 // are averaged.  Positions are FP64 until the polar map, so their error is
 // the FP32 rounding of r and phi (about 1e-7 of the hull radius).
 //
@@ -73,88 +73,128 @@ __device__ __forceinline__ int cyl_steps(double L, double step) {
     return n < 1 ? 1 : n;
 }
 
-// Two radially adjacent nodes (a0, a0 + 1) of one (slice, angle) row.
-template <typename TV>
-__device__ __forceinline__ float2 radial_pair(const TV *__restrict__ vol, int off) {
-    return make_float2(ld(vol, off), ld(vol, off + 1));
+// Lower node and fractions of a lookup at (x, y, z): ring a0 (a0 + 1), angle
+// j0 (the next one modulo n_phi), slice k0 (k0 + 1).
+struct PolarCorner {
+    int a0, j0, k0;
+    float fa, fb, fz;
+};
+
+// atan(t) / t - 1 over t^2 for t in [0, tan(pi/8)], relative error 6e-10 of
+// atan (minimax fit by Remez exchange).
+__device__ __forceinline__ float atan_tail(float s) {
+    float p = fmaf(s, -0.06034788f, 0.10573479f);
+    p = fmaf(s, p, -0.14240083f);
+    p = fmaf(s, p, 0.19998217f);
+    return fmaf(s, p, -0.33333308f);
 }
-typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
-template <>
-__device__ __forceinline__ float2 radial_pair<float>(const float *__restrict__ vol, int off) {
-    const f32x2_a4 p = *reinterpret_cast<const f32x2_a4 *>(vol + off);
-    return make_float2(p.x, p.y);
+
+// The polar map in FP32 (clamped radial and axial index, periodic angle).
+// r = sqrt(x^2 + y^2) from the hardware reciprocal square root with one
+// correction step; the angle within an octant is 2 atan(t), t = min / (r +
+// max) of |x|, |y| (the half angle's tangent, at most tan(pi/8), so a short
+// polynomial serves), also with one correction step of the hardware
+// reciprocal.  Both errors are about an ulp, as the library's sqrtf and atan2f
+// give at four times the instructions: no scaling, no special cases, which
+// finite positions within the hull do not need.  On the axis itself (x = y =
+// 0) r and the angle are 0.
+__device__ __forceinline__ PolarCorner polar_corner(const CylGrid &c, float x, float y, float z) {
+    PolarCorner k;
+    const float v = fmaxf(fmaf(x, x, y * y), 1e-36f);
+    const float rs = __builtin_amdgcn_rsqf(v);
+    float r = v * rs;
+    r = fmaf(fmaf(-r, r, v), 0.5f * rs, r);
+    const float ax = fabsf(x), ay = fabsf(y);
+    const float mn = fminf(ax, ay), den = r + fmaxf(ax, ay);
+    const float rc = __builtin_amdgcn_rcpf(den);
+    float t = mn * rc;
+    t = fmaf(fmaf(-t, den, mn), rc, t);
+    const float s = t * t;
+    float b = fmaf(t * s, atan_tail(s), t) * c.phi_scale2;
+    b = ay > ax ? c.quarter - b : b;
+    b = x < 0.0f ? c.half - b : b;
+    b = y < 0.0f ? c.full - b : b;
+    float bf = floorf(b);
+    k.fb = b - bf;
+    k.j0 = static_cast<int>(bf);
+    if (k.j0 >= c.nphi) k.j0 = 0;   // rounded up to a full turn: fraction 0
+    const float a = fminf(fmaxf(fmaf(r, c.inv_dr, -0.5f), 0.0f), static_cast<float>(c.nr - 1));
+    const float af = fminf(floorf(a), static_cast<float>(c.nr - 2));
+    k.fa = a - af;
+    k.a0 = static_cast<int>(af);
+    const float zz = fminf(fmaxf(fmaf(z, c.inv_dz, c.half_z), 0.0f), static_cast<float>(c.nz - 1));
+    const float zf = fminf(floorf(zz), static_cast<float>(c.nz - 2));
+    k.fz = zz - zf;
+    k.k0 = static_cast<int>(zf);
+    return k;
+}
+
+__device__ __forceinline__ float polar_blend(const PolarCorner &k, float v00, float v01, float v02,
+                                             float v03, float v10, float v11, float v12,
+                                             float v13) {
+    // v?0, v?1: rings a0, a0 + 1 at j0; v?2, v?3: at the next angle
+    const float q00 = fmaf(k.fa, v01 - v00, v00), q01 = fmaf(k.fa, v03 - v02, v02);
+    const float q10 = fmaf(k.fa, v11 - v10, v10), q11 = fmaf(k.fa, v13 - v12, v12);
+    const float s0 = fmaf(k.fb, q01 - q00, q00), s1 = fmaf(k.fb, q11 - q10, q10);
+    return fmaf(k.fz, s1 - s0, s0);
 }
 
 template <typename TV>
 __device__ __forceinline__ float cyl_sample(const TV *__restrict__ vol, const CylGrid &c, float x,
                                             float y, float z) {
-    const float r = sqrtf(fmaf(x, x, y * y));
-    float a = fmaf(r, c.inv_dr, -0.5f);
-    a = fminf(fmaxf(a, 0.0f), static_cast<float>(c.nr - 1));
-    float b = atan2f(y, x) * c.phi_scale;
-    if (b < 0.0f) b += static_cast<float>(c.nphi);
-    float zz = fmaf(z, c.inv_dz, c.half_z);
-    zz = fminf(fmaxf(zz, 0.0f), static_cast<float>(c.nz - 1));
-    const int a0 = min(static_cast<int>(a), c.nr - 2);
-    const int k0 = min(static_cast<int>(zz), c.nz - 2);
-    const float fb_floor = floorf(b);
-    int j0 = static_cast<int>(fb_floor);
-    if (j0 >= c.nphi) j0 -= c.nphi;
-    const int j1 = j0 + 1 == c.nphi ? 0 : j0 + 1;
-    const float fa = a - static_cast<float>(a0), fz = zz - static_cast<float>(k0),
-                fb = b - fb_floor;
+    const PolarCorner k = polar_corner(c, x, y, z);
+    const int j1 = k.j0 + 1 == c.nphi ? 0 : k.j0 + 1;
     const int plane = c.nphi * c.nr;
-    const int base = k0 * plane + a0;
-    const float2 p00 = radial_pair(vol, base + j0 * c.nr);
-    const float2 p01 = radial_pair(vol, base + j1 * c.nr);
-    const float2 p10 = radial_pair(vol, base + plane + j0 * c.nr);
-    const float2 p11 = radial_pair(vol, base + plane + j1 * c.nr);
-    const float q00 = fmaf(fa, p00.y - p00.x, p00.x), q01 = fmaf(fa, p01.y - p01.x, p01.x);
-    const float q10 = fmaf(fa, p10.y - p10.x, p10.x), q11 = fmaf(fa, p11.y - p11.x, p11.x);
-    const float s0 = fmaf(fb, q01 - q00, q00), s1 = fmaf(fb, q11 - q10, q10);
-    return fmaf(fz, s1 - s0, s0);
+    const int b0 = k.k0 * plane + k.j0 * c.nr + k.a0, b1 = k.k0 * plane + j1 * c.nr + k.a0;
+    return polar_blend(k, ld(vol, b0), ld(vol, b0 + 1), ld(vol, b1), ld(vol, b1 + 1),
+                       ld(vol, b0 + plane), ld(vol, b0 + plane + 1), ld(vol, b1 + plane),
+                       ld(vol, b1 + plane + 1));
 }
 
-// The same lookup from the corner-packed copy: the four (ring, angle) corners
-// of slices k0 and k0 + 1 are one 16-byte element each, in the order of the
-// radial pairs above.
-__device__ __forceinline__ float cyl_sample_p4(const float4 *__restrict__ p4, const CylGrid &c,
-                                               float x, float y, float z) {
-    const float r = sqrtf(fmaf(x, x, y * y));
-    float a = fmaf(r, c.inv_dr, -0.5f);
-    a = fminf(fmaxf(a, 0.0f), static_cast<float>(c.nr - 1));
-    float b = atan2f(y, x) * c.phi_scale;
-    if (b < 0.0f) b += static_cast<float>(c.nphi);
-    float zz = fmaf(z, c.inv_dz, c.half_z);
-    zz = fminf(fmaxf(zz, 0.0f), static_cast<float>(c.nz - 1));
-    const int a0 = min(static_cast<int>(a), c.nr - 2);
-    const int k0 = min(static_cast<int>(zz), c.nz - 2);
-    const float fb_floor = floorf(b);
-    int j0 = static_cast<int>(fb_floor);
-    if (j0 >= c.nphi) j0 -= c.nphi;
-    const float fa = a - static_cast<float>(a0), fz = zz - static_cast<float>(k0),
-                fb = b - fb_floor;
-    const int plane = c.nphi * c.nr;
-    const int base = k0 * plane + j0 * c.nr + a0;
-    const float4 e0 = p4[base], e1 = p4[base + plane];
-    const float q00 = fmaf(fa, e0.y - e0.x, e0.x), q01 = fmaf(fa, e0.w - e0.z, e0.z);
-    const float q10 = fmaf(fa, e1.y - e1.x, e1.x), q11 = fmaf(fa, e1.w - e1.z, e1.z);
-    const float s0 = fmaf(fb, q01 - q00, q00), s1 = fmaf(fb, q11 - q10, q10);
-    return fmaf(fz, s1 - s0, s0);
+// The same lookup from a pair-packed copy: two consecutive elements hold the
+// four (ring, angle) corners of a slice, one 16-byte load; slice k0 + 1 is the
+// second.  PHI: the angle-fastest copy.  p1: the copy at slice 1.
+typedef float f32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+template <bool PHI>
+__device__ __forceinline__ float cyl_sample_pairs(const float2 *__restrict__ p0,
+                                                  const float2 *__restrict__ p1, const CylGrid &c,
+                                                  unsigned plane, float x, float y, float z) {
+    const PolarCorner k = polar_corner(c, x, y, z);
+    // 32 x 32 -> 64-bit multiply-adds run at the full rate
+    const unsigned row =
+        PHI ? static_cast<unsigned>(static_cast<unsigned long long>(static_cast<unsigned>(k.a0)) *
+                                        static_cast<unsigned>(c.nphi + 1) +
+                                    static_cast<unsigned>(k.j0))
+            : static_cast<unsigned>(static_cast<unsigned long long>(static_cast<unsigned>(k.j0)) *
+                                        static_cast<unsigned>(c.nr) +
+                                    static_cast<unsigned>(k.a0));
+    const unsigned long long e =
+        static_cast<unsigned long long>(static_cast<unsigned>(k.k0)) * plane + row;
+    const f32x4_a8 v = *reinterpret_cast<const f32x4_a8 *>(p0 + e);
+    const f32x4_a8 w = *reinterpret_cast<const f32x4_a8 *>(p1 + e);
+    return PHI ? polar_blend(k, v.x, v.y, v.z, v.w, w.x, w.y, w.z, w.w)
+               : polar_blend(k, v.x, v.z, v.y, v.w, w.x, w.z, w.y, w.w);
 }
 
-template <typename TV, bool PK>
-__device__ __forceinline__ float cyl_lookup(const TV *__restrict__ vol,
-                                            const float4 *__restrict__ p4, const CylGrid &c,
-                                            float x, float y, float z) {
-    return PK ? cyl_sample_p4(p4, c, x, y, z) : cyl_sample(vol, c, x, y, z);
-}
-
-template <typename TV, int MODE, bool PK>
+// One ray's projection value.  FP32 volumes are read from the two pair-packed
+// copies: where the rays of a wave run mainly towards or away from the axis,
+// they lie side by side in angle and read the angle-fastest copy, where they
+// pass the axis, side by side in radius, the ring-fastest one (decided by the
+// majority of the wave for every four samples); neighbouring lanes then share
+// cache lines.  The values do not depend on the choice.  The SIRT step named
+// below took 8.5 ms with the library's square root and arc tangent and one
+// corner-packed copy, 8.1 ms with polar_corner and the ring-fastest pairs, 6.8
+// with both copies.
+template <typename TV, int MODE>
 __device__ __forceinline__ float cyl_march(const RayGrid &g, const CylGrid &c,
-                                           const TV *__restrict__ vol,
-                                           const float4 *__restrict__ p4, const TileCoord &t) {
+                                           const TV *__restrict__ vol, const FpExtra &ex,
+                                           const TileCoord &t) {
+    constexpr bool PK = sizeof(TV) == 4;   // 16-bit volumes come without copies
     float y = 0.0f;
+    const unsigned plane_r = static_cast<unsigned>(c.nphi) * static_cast<unsigned>(c.nr);
+    const unsigned plane_p = plane_r + static_cast<unsigned>(c.nr);
+    const float2 *const r0 = static_cast<const float2 *>(ex.px), *const r1 = r0 + plane_r;
+    const float2 *const p0 = static_cast<const float2 *>(ex.py), *const p1 = p0 + plane_p;
     for (int s = 0; s < g.n_sub; ++s) {
         const SubView &sv = g.tab[t.p * g.n_sub + s];
         double d[3], t0, t1;
@@ -167,42 +207,66 @@ __device__ __forceinline__ float cyl_march(const RayGrid &g, const CylGrid &c,
             y += static_cast<float>(L);   // n samples of weight h
             continue;
         }
-        // four independent samples per iteration keep several lookups in flight
+        // four independent samples per iteration keep several lookups in
+        // flight; positions are stepped in FP64 (n roundings of 2^-53 stay
+        // far below the FP32 rounding that follows)
+        const double tb = fma(0.5, h, t0);
+        double px = fma(tb, d[0], sv.S[0]), py = fma(tb, d[1], sv.S[1]), pz = fma(tb, d[2], sv.S[2]);
+        const double sx = h * d[0], sy = h * d[1], sz = h * d[2];
+        const float dx = static_cast<float>(d[0]), dy = static_cast<float>(d[1]);
         float acc0 = 0.0f, acc1 = 0.0f, acc2 = 0.0f, acc3 = 0.0f;
+        auto four = [&](auto lookup) {
+            const double x1 = px + sx, y1 = py + sy, z1 = pz + sz;
+            const double x2 = x1 + sx, y2 = y1 + sy, z2 = z1 + sz;
+            const double x3 = x2 + sx, y3 = y2 + sy, z3 = z2 + sz;
+            acc0 += lookup(static_cast<float>(px), static_cast<float>(py), static_cast<float>(pz));
+            acc1 += lookup(static_cast<float>(x1), static_cast<float>(y1), static_cast<float>(z1));
+            acc2 += lookup(static_cast<float>(x2), static_cast<float>(y2), static_cast<float>(z2));
+            acc3 += lookup(static_cast<float>(x3), static_cast<float>(y3), static_cast<float>(z3));
+            px = x3 + sx;
+            py = y3 + sy;
+            pz = z3 + sz;
+        };
+        auto by_ring = [&](float x, float yy, float z) {
+            if constexpr (PK)
+                return cyl_sample_pairs<false>(r0, r1, c, plane_r, x, yy, z);
+            else
+                return cyl_sample(vol, c, x, yy, z);
+        };
+        auto by_angle = [&](float x, float yy, float z) {
+            return cyl_sample_pairs<true>(p0, p1, c, plane_p, x, yy, z);
+        };
         int i = 0;
         for (; i + 3 < n; i += 4) {
-            float xs[4], ys[4], zs[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double tt = fma(i + q + 0.5, h, t0);
-                xs[q] = static_cast<float>(fma(tt, d[0], sv.S[0]));
-                ys[q] = static_cast<float>(fma(tt, d[1], sv.S[1]));
-                zs[q] = static_cast<float>(fma(tt, d[2], sv.S[2]));
+            if constexpr (PK) {
+                const float x = static_cast<float>(px), yy = static_cast<float>(py);
+                const bool radial = fabsf(fmaf(x, dx, yy * dy)) > fabsf(fmaf(x, dy, -yy * dx));
+                if (2 * __popcll(__ballot(radial)) > __popcll(__ballot(true))) {
+                    four(by_angle);
+                    continue;
+                }
             }
-            acc0 += cyl_lookup<TV, PK>(vol, p4, c, xs[0], ys[0], zs[0]);
-            acc1 += cyl_lookup<TV, PK>(vol, p4, c, xs[1], ys[1], zs[1]);
-            acc2 += cyl_lookup<TV, PK>(vol, p4, c, xs[2], ys[2], zs[2]);
-            acc3 += cyl_lookup<TV, PK>(vol, p4, c, xs[3], ys[3], zs[3]);
+            four(by_ring);
         }
         for (; i < n; ++i) {
-            const double tt = fma(i + 0.5, h, t0);
-            acc0 += cyl_lookup<TV, PK>(vol, p4, c, static_cast<float>(fma(tt, d[0], sv.S[0])),
-                                       static_cast<float>(fma(tt, d[1], sv.S[1])),
-                                       static_cast<float>(fma(tt, d[2], sv.S[2])));
+            acc0 += by_ring(static_cast<float>(px), static_cast<float>(py), static_cast<float>(pz));
+            px += sx;
+            py += sy;
+            pz += sz;
         }
         y = fmaf(static_cast<float>(h), (acc0 + acc1) + (acc2 + acc3), y);
     }
     return y / static_cast<float>(g.n_sub);
 }
 
-// Occupancy cap for the FP32 (polar corner-packed) gathers, as for the
-// Cartesian projector: 1104 ms at the 4 waves per SIMD its registers allow,
-// 1014 ms at 3, 932 ms at 2 (256 x 1608 x 512 polar grid, 720 x 768^2,
-// results bitwise identical).  16-bit volumes and the ray-length mode (no
-// gathers) keep the default.
+// Occupancy cap for the FP32 (pair-packed) gathers, as for the Cartesian
+// projector: SIRT step on 96 x 603 x 192 with 120 views of 288^2 6.84 ms at 2
+// waves per SIMD, 6.66 at 3, 6.71 at 4 (100 x 628 x 200, 180 x 300^2: 12.50,
+// 12.40, 13.01).  16-bit volumes and the ray-length mode (no gathers) keep the
+// default.
 template <typename TV, int MODE>
 constexpr int fp_cyl_max_waves() {
-    return (sizeof(TV) == 4 && MODE != FP_RECIP_ONES) ? 2 : 8;
+    return (sizeof(TV) == 4 && MODE != FP_RECIP_ONES) ? 3 : 8;
 }
 
 template <typename TV, typename TS, int MODE>
@@ -214,9 +278,7 @@ void fp_cyl_kernel(RayGrid g, CylGrid c,
     if (!t.valid) return;  // uniform over the block
     const bool active = t.iu < g.n_u && t.iv < g.n_v;
     float y = 0.0f;
-    if (active)
-        y = (MODE != FP_RECIP_ONES && ex.p4) ? cyl_march<TV, MODE, true>(g, c, vol, ex.p4, t)
-                                             : cyl_march<TV, MODE, false>(g, c, vol, nullptr, t);
+    if (active) y = cyl_march<TV, MODE>(g, c, vol, ex, t);
     const int pix = (t.k * g.n_v + t.iv) * g.n_u + t.iu;
     if (MODE == FP_PLAIN) {
         if (active) st(out, pix, y);
@@ -323,7 +385,10 @@ CylGrid make_cyl_grid(int nr, int nphi, int nz, double dr, double dz) {
     c.inv_dr = static_cast<float>(1.0 / dr);
     c.inv_dz = static_cast<float>(1.0 / dz);
     c.half_z = static_cast<float>(0.5 * (nz - 1));
-    c.phi_scale = static_cast<float>(nphi / kTwoPi);
+    c.phi_scale2 = static_cast<float>(2.0 * nphi / kTwoPi);
+    c.full = static_cast<float>(nphi);
+    c.half = static_cast<float>(0.5 * nphi);
+    c.quarter = static_cast<float>(0.25 * nphi);
     const double rh = (nr - 0.5) * dr;
     c.rh2 = rh * rh;
     c.hz = 0.5 * (nz - 1) * dz;

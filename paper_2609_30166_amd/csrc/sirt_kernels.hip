@@ -142,7 +142,9 @@ template <> struct PairOf<uint16_t> {
     }
 };
 
-template <typename T>
+// PERIODIC (polar volumes, x = ring, y = angle): y wraps around, and py's rows
+// hold ny + 1 elements, the last repeating the first.
+template <typename T, bool PERIODIC>
 __global__ __launch_bounds__(THREADS) void pack_pairs_kernel(const T *__restrict__ v,
                                                              typename PairOf<T>::type *__restrict__ px,
                                                              typename PairOf<T>::type *__restrict__ py,
@@ -159,7 +161,8 @@ __global__ __launch_bounds__(THREADS) void pack_pairs_kernel(const T *__restrict
         if (t != blockIdx.x) __syncthreads();   // the previous tile's reads are done
         for (int i = threadIdx.x; i < 33 * 33; i += THREADS) {
             const int j = i / 33, k = i - j * 33;
-            const int x = min(x0 + k, nx - 1), y = min(y0 + j, ny - 1);
+            const int x = min(x0 + k, nx - 1);
+            const int y = PERIODIC ? (y0 + j) % ny : min(y0 + j, ny - 1);
             tile[j][k] = v[plane + static_cast<size_t>(y) * nx + x];
         }
         __syncthreads();
@@ -169,38 +172,25 @@ __global__ __launch_bounds__(THREADS) void pack_pairs_kernel(const T *__restrict
             if (x < nx && y < ny)
                 px[plane + static_cast<size_t>(y) * nx + x] =
                     PairOf<T>::make(tile[j][c], tile[j + 1][c]);
-            const int xt = x0 + j, yt = y0 + c;
-            if (xt < nx && yt < ny)
-                py[plane + static_cast<size_t>(xt) * ny + yt] =
+            const int xt = x0 + j, yt = y0 + c, rows = PERIODIC ? ny + 1 : ny;
+            if (xt < nx && yt < rows)
+                py[(static_cast<size_t>(z) * nx + xt) * rows + yt] =
                     PairOf<T>::make(tile[c][j], tile[c][j + 1]);
         }
     }
 }
 
-__global__ __launch_bounds__(THREADS) void pack_polar_kernel(const float *__restrict__ v,
-                                                             float4 *__restrict__ out, int nr,
-                                                             int nphi, size_t n) {
-    const size_t stride = static_cast<size_t>(gridDim.x) * THREADS;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * THREADS + threadIdx.x; i < n; i += stride) {
-        const int a = static_cast<int>(i % nr);
-        const size_t r = i / nr;
-        const int j = static_cast<int>(r % nphi);
-        const size_t k = r / nphi;
-        const int a1 = min(a + 1, nr - 1), j1 = j + 1 == nphi ? 0 : j + 1;
-        const float *s = v + k * nr * nphi;
-        out[i] = make_float4(s[static_cast<size_t>(j) * nr + a], s[static_cast<size_t>(j) * nr + a1],
-                             s[static_cast<size_t>(j1) * nr + a], s[static_cast<size_t>(j1) * nr + a1]);
-    }
-}
-
 }  // namespace
 
-hipError_t launch_pack_polar(const float *vol, float4 *p4, int nr, int nphi, int nz,
+hipError_t launch_pack_polar(const float *vol, float2 *px, float2 *py, int nr, int nphi, int nz,
                              hipStream_t s) {
-    const size_t n = static_cast<size_t>(nr) * nphi * nz;
-    if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_polar_kernel, dim3(grid_for(n)), dim3(THREADS), 0, s, vol, p4, nr,
-                       nphi, n);
+    if (nr <= 0 || nphi <= 0 || nz <= 0) return hipSuccess;
+    const int tx = (nr + 31) / 32, ty = (nphi + 32) / 32;
+    const unsigned long long all = static_cast<unsigned long long>(tx) * ty * nz;
+    const unsigned tiles = static_cast<unsigned>(all);   // no more than there are voxels: below 2^31
+    const dim3 grid(tiles < (1u << 20) ? tiles : (1u << 20)), block(THREADS);
+    hipLaunchKernelGGL((pack_pairs_kernel<float, true>), grid, block, 0, s, vol, px, py, nr, nphi,
+                       tx, ty, tiles);
     return hipGetLastError();
 }
 
@@ -212,11 +202,11 @@ hipError_t launch_pack_pairs(const void *vol, int dtype, void *px, void *py, int
     const unsigned tiles = static_cast<unsigned>(tx) * static_cast<unsigned>(ty) * static_cast<unsigned>(nz);
     const dim3 grid(tiles < (1u << 20) ? tiles : (1u << 20)), block(THREADS);
     if (dtype == F32)
-        hipLaunchKernelGGL(pack_pairs_kernel<float>, grid, block, 0, s,
+        hipLaunchKernelGGL((pack_pairs_kernel<float, false>), grid, block, 0, s,
                            static_cast<const float *>(vol), static_cast<float2 *>(px),
                            static_cast<float2 *>(py), nx, ny, tx, ty, tiles);
     else
-        hipLaunchKernelGGL(pack_pairs_kernel<uint16_t>, grid, block, 0, s,
+        hipLaunchKernelGGL((pack_pairs_kernel<uint16_t, false>), grid, block, 0, s,
                            static_cast<const uint16_t *>(vol), static_cast<uint32_t *>(px),
                            static_cast<uint32_t *>(py), nx, ny, tx, ty, tiles);
     return hipGetLastError();
