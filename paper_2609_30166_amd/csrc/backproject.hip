@@ -30,6 +30,7 @@
 
 #include "ray_common.h"
 
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -38,14 +39,15 @@ namespace {
 
 using namespace dev;
 
-// Launch shape.  Unwarped: 16 waves per workgroup, one workgroup per CU (its
-// LDS brick and its waves' ray tables take 140 KB of the 160), so 4 waves per
-// SIMD at up to 128 registers, with no spills.  The kernel is bound by LDS
-// instructions, each taking about six CU cycles whatever its number of active
-// lanes, so a hand-over reads the next ray from the table (four 16-byte reads
-// by the lanes that hand over) instead of fifteen full-wave permutes.  Warped:
-// the displacement lookups need the latency hiding of 6 waves per SIMD (12
-// waves per workgroup, two per CU, no table), and hand-overs permute.
+// Launch shape of bp_brick_kernel (the direct form, and the warped owner form
+// where a brick's displacement nodes do not fit in LDS).  Unwarped: 16 waves per
+// workgroup, one workgroup per CU (its LDS brick and its waves' ray tables take
+// 140 KB of the 160), so 4 waves per SIMD at up to 128 registers.  LDS
+// instructions take about six CU cycles whatever their number of active lanes,
+// so a hand-over reads the next ray from the table (four 16-byte reads by the
+// lanes that hand over) instead of fifteen full-wave permutes.  Warped: the
+// displacement loads need the latency hiding of 6 waves per SIMD (12 waves per
+// workgroup, two per CU, no table), and hand-overs permute.
 template <bool WARP> constexpr int bp_threads() { return WARP ? 768 : 1024; }
 template <bool WARP> constexpr bool bp_table() { return !WARP; }
 
@@ -467,37 +469,7 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                     cnext = e.next;
                 }
                 const int trips = (T + 63) >> 6;
-                // the sample walk, with the corner clamps (CLAMP) or without:
-                // in the unwarped owner form a brick that holds neither the
-                // first lower corner 0 nor the last two n - 2, n - 1 on any
-                // axis needs none, since a sample the clamp would move has its
-                // lower corner outside the brick before and after the clamp
-                auto walk = [&](auto clamp_tag) {
-                    constexpr bool CLAMP = decltype(clamp_tag)::value;
-                    // owner form: each lane keeps the eight corner sums of the
-                    // cell its last samples fell in and adds them to LDS only
-                    // when the next sample falls in another cell (consecutive
-                    // samples 0.5 voxel apart often share one), when another
-                    // sample could take a sum past a 32-bit integer, or every
-                    // OWN_MERGE_MAX iterations; the sums are flushed at the end
-                    // of the block, so they hold no registers during the next
-                    // block's ray set-up
-                    int mcell = -1;
-                    float msum = 0.0f;
-                    float m0 = 0.0f, m1 = 0.0f, m2 = 0.0f, m3 = 0.0f;
-                    float m4 = 0.0f, m5 = 0.0f, m6 = 0.0f, m7 = 0.0f;
-                    auto flush = [&]() {
-                        unsigned long long *const f0 = cell0 + mcell;
-                        unsigned long long *const f1 = f0 + OWN_SZ;
-                        atomicAdd(f0, to_fixed(m0));
-                        atomicAdd(f0 + 1, to_fixed(m1));
-                        atomicAdd(f0 + OWN_SY, to_fixed(m2));
-                        atomicAdd(f0 + OWN_SY + 1, to_fixed(m3));
-                        atomicAdd(f1, to_fixed(m4));
-                        atomicAdd(f1 + 1, to_fixed(m5));
-                        atomicAdd(f1 + OWN_SY, to_fixed(m6));
-                        atomicAdd(f1 + OWN_SY + 1, to_fixed(m7));
-                    };
+                {
                     int pos = start;
                     for (int it = 0; it < trips; ++it) {
                         // wave-uniform hand-over to the next ray with samples;
@@ -528,14 +500,10 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                         pz += ctz;
                         int ix, iy, iz;
                         float fx, fy, fz;
-                        if (CLAMP || WARP) {
-                            if (!sample_corner<WARP>(d, w, tau, qx, qy, qz, ix, iy, iz, fx, fy, fz))
-                                continue;
-                        } else {
-                            fx_split(qx, ix, fx);
-                            fx_split(qy, iy, fy);
-                            fx_split(qz, iz, fz);
-                        }
+                        NodeCell nodes;
+                        if (!sample_corner<WARP>(d, w, nodes, tau, qx, qy, qz, ix, iy, iz, fx, fy,
+                                                 fz))
+                            continue;
                         const int lx = ix - x0, ly = iy - y0, lz = iz - z0;
                         if (OWN) {
                             // another brick owns this sample's lower corner
@@ -549,41 +517,16 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                             const float w00 = gz0 * gy0, w01 = gz0 * gy1, w10 = gz1 * gy0,
                                         w11 = gz1 * gy1;
                             const int cell = __mul24(lz, OWN_SZ) + __mul24(ly, OWN_SY) + lx;
-                            if (WARP) {
-                                // warped samples change cells too often for
-                                // the merge to pay (measured 6 % slower):
-                                // add every sample at once
-                                unsigned long long *const a0 = cell0 + cell;
-                                unsigned long long *const a1 = a0 + OWN_SZ;
-                                atomicAdd(a0, to_fixed(w00 * gx0));
-                                atomicAdd(a0 + 1, to_fixed(w00 * gx1));
-                                atomicAdd(a0 + OWN_SY, to_fixed(w01 * gx0));
-                                atomicAdd(a0 + OWN_SY + 1, to_fixed(w01 * gx1));
-                                atomicAdd(a1, to_fixed(w10 * gx0));
-                                atomicAdd(a1 + 1, to_fixed(w10 * gx1));
-                                atomicAdd(a1 + OWN_SY, to_fixed(w11 * gx0));
-                                atomicAdd(a1 + OWN_SY + 1, to_fixed(w11 * gx1));
-                                continue;
-                            }
-                            const float aw = fabsf(cwq);
-                            const bool fresh = (it & (OWN_MERGE_MAX - 1)) == 0;   // uniform
-                            const bool same =
-                                !fresh && cell == mcell && msum + aw <= OWN_MERGE_LIMIT;
-                            if (!same && mcell >= 0) flush();
-                            const float k0 = same ? m0 : 0.0f, k1 = same ? m1 : 0.0f;
-                            const float k2 = same ? m2 : 0.0f, k3 = same ? m3 : 0.0f;
-                            const float k4 = same ? m4 : 0.0f, k5 = same ? m5 : 0.0f;
-                            const float k6 = same ? m6 : 0.0f, k7 = same ? m7 : 0.0f;
-                            m0 = fmaf(w00, gx0, k0);
-                            m1 = fmaf(w00, gx1, k1);
-                            m2 = fmaf(w01, gx0, k2);
-                            m3 = fmaf(w01, gx1, k3);
-                            m4 = fmaf(w10, gx0, k4);
-                            m5 = fmaf(w10, gx1, k5);
-                            m6 = fmaf(w11, gx0, k6);
-                            m7 = fmaf(w11, gx1, k7);
-                            msum = same ? msum + aw : aw;
-                            mcell = cell;
+                            unsigned long long *const a0 = cell0 + cell;
+                            unsigned long long *const a1 = a0 + OWN_SZ;
+                            atomicAdd(a0, to_fixed(w00 * gx0));
+                            atomicAdd(a0 + 1, to_fixed(w00 * gx1));
+                            atomicAdd(a0 + OWN_SY, to_fixed(w01 * gx0));
+                            atomicAdd(a0 + OWN_SY + 1, to_fixed(w01 * gx1));
+                            atomicAdd(a1, to_fixed(w10 * gx0));
+                            atomicAdd(a1 + 1, to_fixed(w10 * gx1));
+                            atomicAdd(a1 + OWN_SY, to_fixed(w11 * gx0));
+                            atomicAdd(a1 + OWN_SY + 1, to_fixed(w11 * gx1));
                             continue;
                         }
                         // no corner in the brick: lx, ly outside [-1, e - 1] (the
@@ -620,14 +563,7 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                         atomicAdd(a1 + LDS_SY, to_fixed(w11 * gx0));
                         atomicAdd(a1 + LDS_SY + 1, to_fixed(w11 * gx1));
                     }
-                    if (OWN && !WARP && mcell >= 0) flush();
-                };
-                const bool interior = OWN && !WARP && x0 >= 1 && x0 + ex <= g.nx - 2 && y0 >= 1 &&
-                                      y0 + ey <= g.ny - 2 && z0 >= 1 && z0 + ez <= g.nz - 2;
-                if (interior)
-                    walk(std::false_type{});
-                else
-                    walk(std::true_type{});
+                }
                 if (TABLE) wave_sync();   // the table is rewritten by the next block
             }
         }
@@ -670,8 +606,9 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
     }
 }
 
-// The unwarped owner form (the default backprojector).  One 16-wave workgroup
-// per CU (its LDS brick and its waves' ray tables take 141 KB of the 160).
+// The owner form (the default backprojector).  One 16-wave workgroup per CU
+// (its LDS brick, its waves' ray tables and, with the warp, its displacement
+// nodes take up to 160 KB).
 //
 // Work is handed out in 8x8 pixel blocks: per batch of 64 (projection,
 // sub-view) pairs, one wave projects the brick onto each pair's detector and
@@ -698,9 +635,103 @@ __device__ __forceinline__ unsigned long long to_fixed_near(float c) {
     return static_cast<unsigned long long>(static_cast<long long>(i));
 }
 
-template <typename TS, int MODE>
+// With the warp, a brick's samples lie within the scan's displacement bound of
+// it, so the displacement nodes around that box are copied to LDS once: the
+// eight 16-byte node loads per sample kept the L1 busy longer than the atomics
+// took.  Nodes in LDS are three planes of floats (x-neighbours are one
+// 8-byte read).  Grids so fine that a brick's nodes exceed OWN_NODES take
+// bp_brick_kernel's loads instead.
+constexpr int OWN_NODES = 1320;
+
+struct NodeBox {
+    int x0, y0, z0;    // first node
+    int nx, ny, nz;    // nodes
+};
+
+// How far (voxels) a walked sample may lie outside its brick's box: the
+// range estimate's margins of 1/64 + 2^-20 i samples (i steps are at most the
+// hull's diagonal) and of 2^-22 of the largest side.
+__host__ __device__ inline double range_slack(const RayGrid &g) {
+    return g.step / 64.0 + (static_cast<double>(g.nx) + g.ny + g.nz) * 0x1p-19;
+}
+
+// Rounding of an FP32 node coordinate of an axis of gn nodes, generously.
+__host__ __device__ inline double node_slack(int gn) { return 1e-3 + gn * 0x1p-20; }
+
+// Nodes that the lookups of positions in [lo - M, hi + M], clipped to the
+// hull, can touch on an axis of n voxels and gn nodes at `scale` nodes per
+// voxel.
+__host__ __device__ inline void node_range(double lo, double hi, double M, int n, int gn,
+                                           double scale, int &first, int &count) {
+    const double a = fmax(lo - M, 0.0) * scale - node_slack(gn);
+    const double b = fmin(hi + M, n - 1.0) * scale + node_slack(gn);
+    const int i0 = static_cast<int>(fmin(fmax(floor(a), 0.0), gn - 2.0));
+    const int i1 = static_cast<int>(fmin(fmax(floor(b), 0.0), gn - 2.0)) + 1;
+    first = i0;
+    count = i1 - i0 + 1;
+}
+
+__device__ inline NodeBox brick_nodes(const WarpGrid &w, const RayGrid &g, int x0, int y0, int z0,
+                                      int ex, int ey, int ez) {
+    NodeBox b;
+    const double M = w.margin + range_slack(g);
+    node_range(x0, x0 + ex, M, g.nx, w.gx, w.sx, b.x0, b.nx);
+    node_range(y0, y0 + ey, M, g.ny, w.gy, w.sy, b.y0, b.ny);
+    node_range(z0, z0 + ez, M, g.nz, w.gz, w.sz, b.z0, b.nz);
+    return b;
+}
+
+// Whether every brick's nodes fit in LDS (on each axis the most over the bricks).
+bool brick_nodes_fit(const WarpGrid &w, const RayGrid &g, const BrickGrid &bg) {
+    const double M = w.margin + range_slack(g);
+    auto most = [&](int size, int bricks, int n, int gn, double scale) {
+        int m = 0;
+        for (int k = 0; k < bricks; ++k) {
+            int first, count;
+            node_range(k * size, k * size + std::min(size, n - k * size), M, n, gn, scale, first,
+                       count);
+            m = std::max(m, count);
+        }
+        return static_cast<long long>(m);
+    };
+    const long long mx = most(bg.bx, bg.nbx, g.nx, w.gx, w.sx);
+    const long long my = most(bg.by, bg.nby, g.ny, w.gy, w.sy);
+    const long long mz = most(bg.bz, bg.nbz, g.nz, w.gz, w.sz);
+    return mx <= OWN_NODES && my <= OWN_NODES && mz <= OWN_NODES && mx * my * mz <= OWN_NODES;
+}
+
+// `displacement` from the nodes in LDS, with the same arithmetic.
+__device__ __forceinline__ float3 lds_displacement(const float *__restrict__ nodes,
+                                                   const NodeBox &nb, const WarpGrid &w, int kx,
+                                                   float fx, int ky, float fy, int kz, float fz) {
+    const float gx = fmaf(fx, w.fsx, static_cast<float>(kx) * w.fsx);
+    const float gy = fmaf(fy, w.fsy, static_cast<float>(ky) * w.fsy);
+    const float gz = fmaf(fz, w.fsz, static_cast<float>(kz) * w.fsz);
+    float ax, ay, az;
+    const int ix = node_corner(gx, w.gx, ax);
+    const int iy = node_corner(gy, w.gy, ay);
+    const int iz = node_corner(gz, w.gz, az);
+    const int sy = nb.nx, sz = __mul24(nb.nx, nb.ny);
+    const float *p = nodes + (__mul24(iz - nb.z0, sz) + __mul24(iy - nb.y0, sy) + (ix - nb.x0));
+    float r[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q, p += OWN_NODES) {
+        const float u000 = p[0], u001 = p[1], u010 = p[sy], u011 = p[sy + 1];
+        const float u100 = p[sz], u101 = p[sz + 1], u110 = p[sz + sy], u111 = p[sz + sy + 1];
+        const float a00 = fmaf(ax, u001 - u000, u000);
+        const float a01 = fmaf(ax, u011 - u010, u010);
+        const float a10 = fmaf(ax, u101 - u100, u100);
+        const float a11 = fmaf(ax, u111 - u110, u110);
+        const float b0 = fmaf(ay, a01 - a00, a00);
+        const float b1 = fmaf(ay, a11 - a10, a10);
+        r[q] = fmaf(az, b1 - b0, b0);
+    }
+    return make_float3(r[0], r[1], r[2]);
+}
+
+template <typename TS, int MODE, bool WARP>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) void bp_own_kernel(
-    RayGrid g, const double *__restrict__ Pmat, const TS *__restrict__ sino,
+    RayGrid g, WarpGrid w, const double *__restrict__ Pmat, const TS *__restrict__ sino,
     const float *__restrict__ rmax, BrickGrid bg) {
     constexpr int NT = 1024;
     __shared__ unsigned long long acc[OWN_CELLS];
@@ -709,6 +740,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     __shared__ int box_v1[OWN_BATCH];
     __shared__ int blk_end[OWN_BATCH];     // inclusive prefix of the block counts
     __shared__ int next_item;
+    __shared__ float nodes[WARP ? 3 * OWN_NODES : 1];
     RayRec *const tabw = rays + (threadIdx.x & ~63);
     const int lane = threadIdx.x & 63;
     // ---- block -> (brick, projection chunk): rows of bricks go to the XCDs
@@ -730,6 +762,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     if (!(cmax > 0.0 && cmax < __builtin_inf()) || x0 > g.nx - 2 || y0 > g.ny - 2 || z0 > g.nz - 2)
         return;
     for (int i = threadIdx.x; i < OWN_CELLS; i += NT) acc[i] = 0ull;
+    NodeBox nb{0, 0, 0, 0, 0, 0};
+    if (WARP) {
+        nb = brick_nodes(w, g, x0, y0, z0, ex, ey, ez);
+        const int count = nb.nx * nb.ny * nb.nz;   // at most OWN_NODES (launch_back)
+        for (int i = threadIdx.x; i < count; i += NT) {
+            const int z = i / (nb.nx * nb.ny), r = i - z * nb.nx * nb.ny;
+            const int y = r / nb.nx, x = r - y * nb.nx;
+            const float4 u = w.U[((nb.z0 + z) * w.gy + nb.y0 + y) * w.gx + nb.x0 + x];
+            nodes[i] = u.x;
+            nodes[OWN_NODES + i] = u.y;
+            nodes[2 * OWN_NODES + i] = u.z;
+        }
+    }
     const double scale = uni(ldexp(1.0, uni(own_kexp(cmax, g, bg.cube_samples))));
     const double off[3] = {0.5 * (g.nx - 1), 0.5 * (g.ny - 1), 0.5 * (g.nz - 1)};
     // 1 / n_sub and the caller's factor (1 unless scaled; exact when a power of 2)
@@ -737,16 +782,54 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     // largest side times 2^-22: four times the FP32 rounding error of a
     // coordinate of a ray's start (the ray-range estimate is widened by it)
     const float tol = uni(static_cast<float>(max(g.nx, max(g.ny, g.nz))) * 2.38418579e-7f);
-    const float lo[3] = {uni(x0 - tol), uni(y0 - tol), uni(z0 - tol)};
-    const float hi[3] = {uni(static_cast<float>(x0 + ex) + tol),
-                         uni(static_cast<float>(y0 + ey) + tol),
-                         uni(static_cast<float>(z0 + ez) + tol)};
+    const float lo0[3] = {uni(x0 - tol), uni(y0 - tol), uni(z0 - tol)};
+    const float hi0[3] = {uni(static_cast<float>(x0 + ex) + tol),
+                          uni(static_cast<float>(y0 + ey) + tol),
+                          uni(static_cast<float>(z0 + ez) + tol)};
+    // With the warp, samples that can land in the brick start within [lo0 -
+    // max tau U, hi0 - min tau U], U between the least and the largest of the
+    // brick's nodes (a trilinear value lies between its nodes).  Bounded by
+    // the whole field's largest component instead, a brick of the helical scan
+    // walked about twice the samples it owned.
+    float un[3] = {0.0f, 0.0f, 0.0f}, ux[3] = {0.0f, 0.0f, 0.0f};
+    if (WARP) {
+        __syncthreads();
+        const int count = nb.nx * nb.ny * nb.nz;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            float mn = __builtin_inff(), mxv = -__builtin_inff();
+            for (int i = lane; i < count; i += 64) {
+                mn = fminf(mn, nodes[a * OWN_NODES + i]);
+                mxv = fmaxf(mxv, nodes[a * OWN_NODES + i]);
+            }
+            for (int o = 32; o > 0; o >>= 1) {
+                mn = fminf(mn, __shfl_xor(mn, o, 64));
+                mxv = fmaxf(mxv, __shfl_xor(mxv, o, 64));
+            }
+            un[a] = uni(mn);
+            ux[a] = uni(mxv);
+        }
+    }
+    // the range of starting positions for a sub-view (the allowance covers
+    // the FP32 rounding of the displaced position)
+    auto range = [&](float tau, float (&lo)[3], float (&hi)[3]) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float p = tau * un[a], q = tau * ux[a];
+            const float e = WARP ? 1e-5f * (1.0f + fabsf(p) + fabsf(q)) : 0.0f;
+            lo[a] = lo0[a] - fmaxf(p, q) - e;
+            hi[a] = hi0[a] - fminf(p, q) + e;
+        }
+    };
     // owned lower corners, relative to the brick: [0, e) on every axis, open
     // towards the faces, where the clamp moves corners into the brick
     const int mx = g.nx - 2 - x0, my = g.ny - 2 - y0, mz = g.nz - 2 - z0;
     const int ax = x0 == 0 ? INT_MIN : 0, bx = mx < ex ? INT_MAX : ex - 1;
     const int ay = y0 == 0 ? INT_MIN : 0, by = my < ey ? INT_MAX : ey - 1;
     const int az = z0 == 0 ? INT_MIN : 0, bz = mz < ez ? INT_MAX : ez - 1;
+    // with the warp: owned corners [0, w), none past n - 2
+    const int wx = min(ex, mx + 1), wy = min(ey, my + 1), wz = min(ez, mz + 1);
+    const bool last = mx < ex || my < ey || mz < ez;   // it holds a corner n - 2
     // no clamp can act where the brick holds neither the first lower corner
     // nor the last
     const bool interior = x0 >= 1 && mx >= ex && y0 >= 1 && my >= ey && z0 >= 1 && mz >= ez;
@@ -762,6 +845,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 const int k = k_first + q / g.n_sub;
                 const int p = g.views ? g.views[k] : k;
                 const int sv_idx = p * g.n_sub + q % g.n_sub;
+                float lo[3], hi[3];
+                range(static_cast<float>(g.tab[sv_idx].tau), lo, hi);
                 const double plo[3] = {lo[0], lo[1], lo[2]}, phi[3] = {hi[0], hi[1], hi[2]};
                 int u0 = 0, u1 = g.n_u - 1, v0 = 0, v1 = g.n_v - 1;
                 if (!project_box(Pmat + 12 * static_cast<size_t>(sv_idx), plo, phi, off, g.n_u,
@@ -798,6 +883,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
             const int k = k_first + kq;
             const int p = uni(g.views ? g.views[k] : k);
             const SubView &sv = g.tab[p * g.n_sub + (q - kq * g.n_sub)];
+            const float tau = WARP ? uni(static_cast<float>(sv.tau)) : 0.0f;
+            float lo[3], hi[3];
+            range(tau, lo, hi);
             const int bv = blk / bu;
             const int iv = v0 + bv * 8 + (lane >> 3);
             const int iu = u0 + (blk - bv * bu) * 8 + (lane & 7);
@@ -836,10 +924,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                     kmax = flat ? kmax : fminf(kmax, th + mh);
                     hit &= !(flat & ((bv3[a] < lo[a]) | (bv3[a] > hi[a])));
                 }
-                // positions relative to the brick
-                r.qx -= static_cast<long long>(x0) << FX;
-                r.qy -= static_cast<long long>(y0) << FX;
-                r.qz -= static_cast<long long>(z0) << FX;
+                // positions relative to the brick (of the volume with the
+                // warp, whose lookup comes first)
+                if (!WARP) {
+                    r.qx -= static_cast<long long>(x0) << FX;
+                    r.qy -= static_cast<long long>(y0) << FX;
+                    r.qz -= static_cast<long long>(z0) << FX;
+                }
                 if (hit && kmin <= kmax) {
                     ib = max(static_cast<int>(ceilf(kmin)), 0);
                     int ie = min(static_cast<int>(floorf(kmax)), r.n - 1);
@@ -851,8 +942,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                         const int kz = static_cast<int>((r.qz + i * r.tz) >> FX);
                         return kx >= ax && kx <= bx && ky >= ay && ky <= by && kz >= az && kz <= bz;
                     };
-                    while (ib <= ie && !owned(ib)) ++ib;
-                    while (ib <= ie && !owned(ie)) --ie;
+                    if (!WARP) {
+                        while (ib <= ie && !owned(ib)) ++ib;
+                        while (ib <= ie && !owned(ie)) --ie;
+                    }
                     len = max(ie - ib + 1, 0);
                     wq = static_cast<float>(static_cast<double>(r.h * rv * inv_sub) * scale);
                 }
@@ -988,7 +1081,68 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 if (pos < end) sample();
                 if (start < end) flush();
             };
-            if (interior)
+            // With the warp a sample's corner, and whether the brick owns it, is
+            // known only after the displacement lookup, and samples change
+            // cells too often for the merge to pay: each is added at once.
+            auto walk_warped = [&]() {
+                auto sample = [&]() {
+                    if (pos == c.end) c = tabw[c.next];   // enter the next ray
+                    ++pos;
+                    int kx, ky, kz;
+                    float lx, ly, lz;
+                    fx_split(c.px, kx, lx);
+                    fx_split(c.py, ky, ly);
+                    fx_split(c.pz, kz, lz);
+                    c.px += c.tx;
+                    c.py += c.ty;
+                    c.pz += c.tz;
+                    const float3 u = lds_displacement(nodes, nb, w, kx, lx, ky, ly, kz, lz);
+                    lx = fmaf(tau, u.x, lx);
+                    ly = fmaf(tau, u.y, ly);
+                    lz = fmaf(tau, u.z, lz);
+                    // lower corner relative to the brick; one outside the hull
+                    // is owned by no brick
+                    const float flx = floorf(lx), fly = floorf(ly), flz = floorf(lz);
+                    int ox = kx + static_cast<int>(flx) - x0;
+                    int oy = ky + static_cast<int>(fly) - y0;
+                    int oz = kz + static_cast<int>(flz) - z0;
+                    float fx = lx - flx, fy = ly - fly, fz = lz - flz;
+                    if (last) {   // uniform: corner n - 1 with weight 0 beyond it
+                        auto face = [](int &o, float &f, int m) {
+                            if (o == m + 1 && f == 0.0f) {
+                                o = m;
+                                f = 1.0f;
+                            }
+                        };
+                        face(ox, fx, mx);
+                        face(oy, fy, my);
+                        face(oz, fz, mz);
+                    }
+                    if (static_cast<uint32_t>(ox) >= static_cast<uint32_t>(wx) ||
+                        static_cast<uint32_t>(oy) >= static_cast<uint32_t>(wy) ||
+                        static_cast<uint32_t>(oz) >= static_cast<uint32_t>(wz))
+                        return;
+                    const float gx0 = 1.0f - fx;
+                    const float gz1 = fz * c.wq, gz0 = c.wq - gz1;
+                    const float w01 = gz0 * fy, w00 = gz0 - w01, w11 = gz1 * fy, w10 = gz1 - w11;
+                    unsigned long long *const f0 =
+                        acc + (__mul24(oz, OWN_SZ) + (__mul24(oy, OWN_SY) + ox));
+                    unsigned long long *const f1 = f0 + OWN_SZ;
+                    atomicAdd(f0, to_fixed_near(w00 * gx0));
+                    atomicAdd(f0 + 1, to_fixed_near(w00 * fx));
+                    atomicAdd(f0 + OWN_SY, to_fixed_near(w01 * gx0));
+                    atomicAdd(f0 + OWN_SY + 1, to_fixed_near(w01 * fx));
+                    atomicAdd(f1, to_fixed_near(w10 * gx0));
+                    atomicAdd(f1 + 1, to_fixed_near(w10 * fx));
+                    atomicAdd(f1 + OWN_SY, to_fixed_near(w11 * gx0));
+                    atomicAdd(f1 + OWN_SY + 1, to_fixed_near(w11 * fx));
+                };
+                for (int it = T >> 6; it > 0; --it) sample();
+                if (pos < end) sample();
+            };
+            if constexpr (WARP)
+                walk_warped();
+            else if (interior)
                 walk(std::false_type{});
             else
                 walk(std::true_type{});
@@ -1099,7 +1253,8 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
     const bool wp = w.U != nullptr;
     const dim3 grid(static_cast<unsigned>(per * N_XCD));
     const dim3 block(static_cast<unsigned>(wp ? bp_threads<true>() : bp_threads<false>()));
-    // unwarped owner form: whole rows of bricks, a multiple of N_XCD rows
+    const bool nodes_fit = wp && !direct && brick_nodes_fit(w, g, bg);
+    // owner form: whole rows of bricks, a multiple of N_XCD rows
     const int rows = (bg.nby * bg.nbz + N_XCD - 1) / N_XCD * N_XCD;
     const dim3 own_grid(static_cast<unsigned>(rows) * bg.nbx * bg.chunks);
     const size_t shmem = 0;   // the brick is static LDS
@@ -1137,12 +1292,15 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
                 hipLaunchKernelGGL((bp_brick_kernel<T, M, false, false>), grid, block, shmem,   \
                                    stream, g, w, Pmat, SP, RM, vol, bg);                        \
         } else {                                                                                \
-            if (wp)                                                                             \
+            if (wp && !nodes_fit)                                                               \
                 hipLaunchKernelGGL((bp_brick_kernel<T, M, true, true>), grid, block, shmem,     \
                                    stream, g, w, Pmat, SP, RM, vol, bg);                        \
+            else if (wp)                                                                        \
+                hipLaunchKernelGGL((bp_own_kernel<T, M, true>), own_grid, dim3(1024), 0,        \
+                                   stream, g, w, Pmat, SP, RM, bg);                             \
             else                                                                                \
-                hipLaunchKernelGGL((bp_own_kernel<T, M>), own_grid, block, 0, stream, g, Pmat,  \
-                                   SP, RM, bg);                                                 \
+                hipLaunchKernelGGL((bp_own_kernel<T, M, false>), own_grid, dim3(1024), 0,       \
+                                   stream, g, w, Pmat, SP, RM, bg);                             \
         }                                                                                       \
         return finish(M);                                                                       \
     }

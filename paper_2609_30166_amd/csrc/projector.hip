@@ -82,11 +82,12 @@ __device__ __forceinline__ float gather_pairs(const void *__restrict__ pk, const
 // inside and 0 outside).  TL: `pk` is the y-fastest copy.
 template <typename TV, int MODE, bool WARP, bool TL>
 __device__ __forceinline__ float sample_value(const void *__restrict__ pk, const VolDims &d,
-                                              const WarpGrid &w, float tau, long long px,
+                                              const WarpGrid &w, NodeCell &cell, float tau,
+                                              long long px,
                                               long long py, long long pz) {
     int ix, iy, iz;
     Corner k;
-    const bool in = sample_corner<WARP>(d, w, tau, px, py, pz, ix, iy, iz, k.fx, k.fy, k.fz);
+    const bool in = sample_corner<WARP>(d, w, cell, tau, px, py, pz, ix, iy, iz, k.fx, k.fy, k.fz);
     if (MODE == FP_RECIP_ONES) return in ? 1.0f : 0.0f;
     k.base = TL ? base_t(d, ix, iy, iz) : base_x(d, ix, iy, iz);
     const float v = gather_pairs<TV, TL>(pk, d, k);
@@ -162,14 +163,15 @@ __device__ __forceinline__ float ray_sum(const VolDims &d, const WarpGrid &w, fl
             return acc0 + acc1;
         }
     }
+    NodeCell cell;
     for (; i + 1 < r.n; i += 2) {
-        acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
-        acc1 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px + r.tx, py + r.ty, pz + r.tz);
+        acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, cell, tau, px, py, pz);
+        acc1 += sample_value<TV, MODE, WARP, TL>(pk, d, w, cell, tau, px + r.tx, py + r.ty, pz + r.tz);
         px += 2 * r.tx;
         py += 2 * r.ty;
         pz += 2 * r.tz;
     }
-    if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, tau, px, py, pz);
+    if (i < r.n) acc0 += sample_value<TV, MODE, WARP, TL>(pk, d, w, cell, tau, px, py, pz);
     return acc0 + acc1;
 }
 
@@ -275,7 +277,8 @@ __device__ float march_tube(const RayGrid &g, const float *__restrict__ vol, con
                              bool lds) {
             int ix, iy, iz;
             Corner k;
-            sample_corner<false>(d, WarpGrid{}, 0.0f, px, py, pz, ix, iy, iz, k.fx, k.fy, k.fz);
+            NodeCell none;
+            sample_corner<false>(d, WarpGrid{}, none, 0.0f, px, py, pz, ix, iy, iz, k.fx, k.fy, k.fz);
             // a corner outside the staged box (never, if the bound holds)
             // falls back to the global gather
             lds = lds && static_cast<unsigned>(ix - x0) < static_cast<unsigned>(lx - 1) &&

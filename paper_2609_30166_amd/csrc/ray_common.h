@@ -136,13 +136,11 @@ struct Corner {
     float fx, fy, fz;   // fractions in [0, 1]
 };
 
-// Lower corner and fraction on one axis of n >= 2 nodes for the position
-// i + l (i integer, l the FP32 local offset), as for the coordinate clamped
-// into [0, n - 1] with corner min(floor(c), n - 2).
-__device__ __forceinline__ void axis_corner(int i, float l, int n, int &k, float &f) {
-    const float fl = floorf(l);
-    k = i + static_cast<int>(fl);
-    f = l - fl;
+// Corner k and fraction f of a warped coordinate outside [0, n - 2] on some
+// axis: true if it lies in [0, n - 1] on this one, with the last face turned
+// into weight 1 on corner n - 2; the corner is clamped into the grid either way.
+__device__ __forceinline__ bool axis_last(int &k, float &f, int n) {
+    const bool in = k >= 0 && (k < n - 1 || (k == n - 1 && f == 0.0f));
     if (k < 0) {
         k = 0;
         f = 0.0f;
@@ -151,16 +149,10 @@ __device__ __forceinline__ void axis_corner(int i, float l, int n, int &k, float
         k = n - 2;
         f = 1.0f;
     }
+    return in;
 }
 
-// True when i + l lies in [0, n - 1].
-__device__ __forceinline__ bool axis_inside(int i, float l, int n) {
-    const float fl = floorf(l);
-    const int k = i + static_cast<int>(fl);
-    return k >= 0 && (k < n - 1 || (k == n - 1 && l == fl));
-}
-
-// The same for a position already split into k + f with f in [0, 1): only
+// Corner of an unwarped position already split into k + f with f in [0, 1]:
 // the clamps (k < 0 rounds onto the first corner with weight 0 on the next;
 // k > n - 2 is the last face, weight 1 on it).
 __device__ __forceinline__ void axis_clamp(int k, float f, int n, int &kc, float &fc) {
@@ -223,41 +215,64 @@ __device__ __forceinline__ int base_t(const VolDims &d, int ix, int iy, int iz) 
 }
 
 // ----------------------------------------------------------------- warp ----
+// Lower node and fraction of a node coordinate on an axis of n >= 2 nodes,
+// clamped to [0, n - 1] (a coordinate of n - 1 is weight 1 on the last node).
+__device__ __forceinline__ int node_corner(float c, int n, float &f) {
+    c = fminf(fmaxf(c, 0.0f), static_cast<float>(n - 1));
+    const int k = min(static_cast<int>(c), n - 2);
+    f = c - static_cast<float>(k);
+    return k;
+}
+
+// The eight displacement nodes of one grid cell, by component; node j is the
+// x (bit 0), y (bit 1), z (bit 2) neighbour of the lower one.
+struct NodeCell {
+    int b = -1;        // index of the lower node
+    float u[3][8];
+    // a cell spans several voxels, so consecutive samples mostly share one
+    __device__ __forceinline__ void load(const WarpGrid &w, int base) {
+        if (base == b) return;
+        b = base;
+        const float4 *const p = w.U + base;
+        const int sy = w.gx, sz = w.gx * w.gy;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float4 v = p[(j & 1) + ((j & 2) ? sy : 0) + ((j & 4) ? sz : 0)];
+            u[0][j] = v.x;
+            u[1][j] = v.y;
+            u[2][j] = v.z;
+        }
+    }
+};
+
 // Displacement at the sample k + f (per axis: integer voxel and fraction):
 // the node grid coordinate (k + f) (g - 1) / (n - 1) is formed in FP32 (it
 // is at most g - 1, so its rounding is ~2^-19 of a grid cell) and U is
-// interpolated trilinearly there, lookups clamped to the grid.
-__device__ __forceinline__ float3 displacement(const WarpGrid &w, int kx, float fx, int ky,
-                                               float fy, int kz, float fz) {
+// interpolated trilinearly there, lookups clamped to the grid.  `cell` holds
+// the nodes of the last sample's cell.
+__device__ __forceinline__ float3 displacement(const WarpGrid &w, NodeCell &cell, int kx, float fx,
+                                               int ky, float fy, int kz, float fz) {
     const float gx = fmaf(fx, w.fsx, static_cast<float>(kx) * w.fsx);
     const float gy = fmaf(fy, w.fsy, static_cast<float>(ky) * w.fsy);
     const float gz = fmaf(fz, w.fsz, static_cast<float>(kz) * w.fsz);
-    int ix, iy, iz;
     float ax, ay, az;
-    axis_corner(0, gx, w.gx, ix, ax);
-    axis_corner(0, gy, w.gy, iy, ay);
-    axis_corner(0, gz, w.gz, iz, az);
-    const int sy = w.gx, sz = w.gx * w.gy;
-    const int b = (iz * w.gy + iy) * w.gx + ix;
-    const float4 u000 = w.U[b], u001 = w.U[b + 1], u010 = w.U[b + sy], u011 = w.U[b + sy + 1];
-    const float4 u100 = w.U[b + sz], u101 = w.U[b + sz + 1];
-    const float4 u110 = w.U[b + sz + sy], u111 = w.U[b + sz + sy + 1];
-    float3 r;
-#define CTREX_LERP3(c)                                              \
-    {                                                               \
-        const float a00 = fmaf(ax, u001.c - u000.c, u000.c);        \
-        const float a01 = fmaf(ax, u011.c - u010.c, u010.c);        \
-        const float a10 = fmaf(ax, u101.c - u100.c, u100.c);        \
-        const float a11 = fmaf(ax, u111.c - u110.c, u110.c);        \
-        const float b0 = fmaf(ay, a01 - a00, a00);                  \
-        const float b1 = fmaf(ay, a11 - a10, a10);                  \
-        r.c = fmaf(az, b1 - b0, b0);                                \
+    const int ix = node_corner(gx, w.gx, ax);
+    const int iy = node_corner(gy, w.gy, ay);
+    const int iz = node_corner(gz, w.gz, az);
+    cell.load(w, (iz * w.gy + iy) * w.gx + ix);
+    float r[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const float(&u)[8] = cell.u[q];
+        const float a00 = fmaf(ax, u[1] - u[0], u[0]);
+        const float a01 = fmaf(ax, u[3] - u[2], u[2]);
+        const float a10 = fmaf(ax, u[5] - u[4], u[4]);
+        const float a11 = fmaf(ax, u[7] - u[6], u[6]);
+        const float b0 = fmaf(ay, a01 - a00, a00);
+        const float b1 = fmaf(ay, a11 - a10, a10);
+        r[q] = fmaf(az, b1 - b0, b0);
     }
-    CTREX_LERP3(x)
-    CTREX_LERP3(y)
-    CTREX_LERP3(z)
-#undef CTREX_LERP3
-    return r;
+    return make_float3(r[0], r[1], r[2]);
 }
 
 // Lower corner (ix, iy, iz) and fractions of the sample at fixed-point
@@ -268,8 +283,8 @@ __device__ __forceinline__ float3 displacement(const WarpGrid &w, int kx, float 
 // projectors call this one function, so their corners and weights agree bit
 // for bit.
 template <bool WARP>
-__device__ __forceinline__ bool sample_corner(const VolDims &d, const WarpGrid &w, float tau,
-                                              long long px, long long py, long long pz, int &ix,
+__device__ __forceinline__ bool sample_corner(const VolDims &d, const WarpGrid &w, NodeCell &cell,
+                                              float tau, long long px, long long py, long long pz, int &ix,
                                               int &iy, int &iz, float &fx, float &fy,
                                               float &fz) {
     int kx, ky, kz;
@@ -278,15 +293,24 @@ __device__ __forceinline__ bool sample_corner(const VolDims &d, const WarpGrid &
     fx_split(py, ky, ly);
     fx_split(pz, kz, lz);
     if (WARP) {
-        const float3 u = displacement(w, kx, lx, ky, ly, kz, lz);
+        const float3 u = displacement(w, cell, kx, lx, ky, ly, kz, lz);
         lx = fmaf(tau, u.x, lx);
         ly = fmaf(tau, u.y, ly);
         lz = fmaf(tau, u.z, lz);
-        const bool in =
-            axis_inside(kx, lx, d.nx) && axis_inside(ky, ly, d.ny) && axis_inside(kz, lz, d.nz);
-        axis_corner(kx, lx, d.nx, ix, fx);
-        axis_corner(ky, ly, d.ny, iy, fy);
-        axis_corner(kz, lz, d.nz, iz, fz);
+        const float ex = floorf(lx), ey = floorf(ly), ez = floorf(lz);
+        ix = kx + static_cast<int>(ex);
+        iy = ky + static_cast<int>(ey);
+        iz = kz + static_cast<int>(ez);
+        fx = lx - ex;
+        fy = ly - ey;
+        fz = lz - ez;
+        const bool cell = static_cast<unsigned>(ix) <= static_cast<unsigned>(d.nx - 2) &&
+                          static_cast<unsigned>(iy) <= static_cast<unsigned>(d.ny - 2) &&
+                          static_cast<unsigned>(iz) <= static_cast<unsigned>(d.nz - 2);
+        if (cell) return true;
+        // on the last face (weight 1 on the last cell's upper corner), or
+        // outside the hull
+        const bool in = axis_last(ix, fx, d.nx) & axis_last(iy, fy, d.ny) & axis_last(iz, fz, d.nz);
         return in;
     } else {
         axis_clamp(kx, lx, d.nx, ix, fx);
