@@ -227,21 +227,39 @@ __global__ __launch_bounds__(NT) void conv3_c1_tile_kernel(const u16 *__restrict
 // bytes per element, so the 16 lanes of an MFMA row group read 256 contiguous
 // bytes.  Each A fragment of the GEMM is then one LDS read instead of a
 // gather through L1/L2 (every input voxel feeds 27 taps); weights come from
-// global memory (the same for every wave, so from the cache).  A wave owns
-// MBW consecutive y rows of one z plane, so every LDS offset but the lane's
-// base is a compile-time constant.  More than 32 input channels are staged
+// global memory, through the L1.  A wave owns MBW consecutive y rows of one z
+// plane, so every LDS offset but the lane's base is a compile-time constant,
+// and NB blocks of 16 output channels.
+//
+// The weight reads bound these kernels: the four lanes of a quad read 16 bytes
+// of four different output channels, so one fragment takes the L1 about 32
+// accesses, for the MBW matrix instructions that it feeds (the address unit
+// was busy 63 to 77 % of the time).  So a wave takes 8 rows where it can, each fragment feeding 8
+// instructions: with 32 or 64 outputs (and 32 or 64 inputs) the four waves
+// split NW = 2 ways over the output channels and 2 ways over the rows, with
+// 32 -> 16 the tile has four planes.  Times at 256^3 (64 -> 64: the 64^3
+// level of it), 4 rows a wave and now: 32 -> 16 of a concatenation 985 and 880
+// us, 64 -> 32 of one 525 and 340, 32 -> 32 182 and 138, 64 -> 64 133 and 86,
+// 32 -> 64 58 and 37.  16 -> 32 did not gain (89 and 96 us) and keeps all
+// channels per wave.  Measured slower: the weights of a workgroup in LDS
+// (32 -> 16 1450 us, 16 -> 16 435 to 490: fewer workgroups fit), and in
+// registers over a loop of tiles (they spill, or halve the waves).  More than 32 input channels are staged
 // and contracted 32 at a time (the tile keeps the 32-channel shape and LDS
 // size: 64 channels at once would need a 4 x 2 tile, three times as many
 // halo voxels per output, and half the workgroups per CU).  Occupancy hints:
-// 16 -> 16 runs 4 waves per SIMD in 128 registers; 32 or 64 inputs with at
-// most 32 outputs run 3 (the LDS tile admits three workgroups per CU); 64
-// outputs with 32 or 64 inputs run 2 (without the hint the 64 -> 64 tile's
-// two epilogue forms took just over 256 registers, one wave per SIMD); 16 ->
-// 32 takes what its accumulators leave.  Tiles: 8 x 4 rows for 16 -> 16,
-// 8 x 2 otherwise (16 -> 32 measured 0.83 -> 0.70 ms as a data gradient at
-// 256^3 with 8 x 2, 16 -> 16 0.46 -> 0.49 ms, so each keeps its faster shape).
+// 16 -> 16 runs 4 waves per SIMD in 128 registers; 32 or 64 inputs with 32
+// outputs run 3 (the LDS tile admits three workgroups per CU), 32 -> 16 runs
+// 2 (its four-plane tile admits two); 64 outputs with 32 or 64 inputs run 2
+// (without the hint the 64 -> 64 tile's two epilogue forms took just over 256
+// registers, one wave per SIMD); 16 -> 32 takes what its accumulators leave.
+// Tiles: 8 x 4 rows for 16 outputs, 8 x 2 otherwise (16 -> 32 measured 0.83 ->
+// 0.70 ms as a data gradient at 256^3 with 8 x 2, 16 -> 16 0.46 -> 0.49 ms, so
+// each keeps its faster shape).
 template <int CIN, int COUT> struct ConvTile {
-    static constexpr int TY = 8, TZ = CIN == 16 && COUT == 16 ? 4 : 2;
+    static constexpr int TY = 8, TZ = COUT == 16 ? 4 : 2;
+    static constexpr int NW = CIN == 16 || COUT == 16 ? 1 : 2;   // waves over the outputs
+    static constexpr int NB = COUT / 16 / NW;   // 16-channel output blocks per wave
+    static constexpr int WAVES = CIN == 16 ? (COUT == 16 ? 4 : 1) : (COUT == 32 ? 3 : 2);
 };
 
 // Second input and output of a convolution over a channel concatenation: input
@@ -274,7 +292,7 @@ struct HeadArgs {
 
 template <int CIN, int COUT, bool OUT_F32, bool RELU, bool ACC, bool CAT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
-    CIN == 16 ? (COUT == 16 ? 4 : 1) : (COUT <= 32 ? 3 : 2)))) void
+    ConvTile<CIN, COUT>::WAVES))) void
 conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *__restrict__ wt,
                   const float *__restrict__ bias, void *out, int out_cs, int out_off, int D, int H,
                   int W, int out_vec, CatArgs cat, HeadArgs head) {
@@ -283,8 +301,8 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
     constexpr int NH = CIN / CST;             // staging passes
     constexpr int SX = 18, SY = TY + 2, SZ = TZ + 2, NC = CST / 8;
     constexpr int NEL = SZ * SY * NC * SX;   // 16-byte elements
-    constexpr int MBW = TY * TZ / (NT / 64);  // rows per wave
-    constexpr int NB = COUT / 16;
+    constexpr int NW = ConvTile<CIN, COUT>::NW, NB = ConvTile<CIN, COUT>::NB;
+    constexpr int MBW = TY * TZ / (NT / 64 / NW);  // rows per wave
     static_assert(TY % MBW == 0, "a wave's rows lie in one z plane");
     __shared__ bf16x8 tile[NEL];
 
@@ -295,7 +313,8 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
     const int y0 = (bi % nty) * TY, z0 = (bi / nty) * TZ;
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, r = lane & 15;
-    const int row0 = wave * MBW;                 // first row (y + TY z) of this wave
+    const int row0 = wave / NW * MBW;            // first row (y + TY z) of this wave
+    const int nb0 = wave % NW * NB;              // first output block of this wave
     const int ym0 = row0 % TY, zm = row0 / TY;
     // element of (row ym0, plane zm, chunk 0, x = r), tap (0, 0, 0)
     const int lbase = (((zm + 1) * SY + ym0 + 1) * NC) * SX + r + 1;
@@ -370,7 +389,7 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
         // instead of being hoisted out of it and held in registers
         const u16 *wh = wt + h * CST;
         if (NH > 1) asm volatile("" : "+v"(wh));
-        if constexpr (CIN == 16 || NB > 2) {
+        if constexpr (CIN == 16 || COUT > 32) {
             // K steps: for 16 channels pairs of taps (lane groups 0, 1 take tap 2p,
             // channel chunks 0, 1; groups 2, 3 tap 2p + 1; tap 27 is zero padding),
             // otherwise one tap and 32 channels per step.  The fragments of step
@@ -387,7 +406,7 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
                 for (int m = 0; m < MBW; ++m) a[m] = live ? tile[off + m * NC * SX] : zero8();
 #pragma unroll
                 for (int n = 0; n < NB; ++n)
-                    b[n] = live ? load8(wh + (tap * COUT + n * 16 + r) * CIN + 8 * c) : zero8();
+                    b[n] = live ? load8(wh + (tap * COUT + (nb0 + n) * 16 + r) * CIN + 8 * c) : zero8();
             };
             auto step = [&](const bf16x8 (&a)[MBW], const bf16x8 (&b)[NB]) {
 #pragma unroll
@@ -416,8 +435,8 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
             // LDS read feeds up to three MFMA blocks instead of one.  The
             // next row's fragment (and, at the first row of a (dz, dx), the
             // next pair's weights) is read while the current MFMAs run.
-            constexpr int NR = MBW + 2, NS = 9 * NR;
-            static_assert(NR % 2 == 0, "rows are taken in pairs");
+            constexpr int NR = MBW + 2;
+            static_assert(NR % 2 == 0, "the two row registers alternate across pairs");
             auto fetch_b = [&](int q, bf16x8 (&b)[3][NB]) {
                 const int dz = q / 3 - 1, dx = q % 3 - 1;
 #pragma unroll
@@ -425,39 +444,36 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
                     const int tap = (dz + 1) * 9 + dyi * 3 + dx + 1;
 #pragma unroll
                     for (int n = 0; n < NB; ++n)
-                        b[dyi][n] = load8(wh + (tap * COUT + n * 16 + r) * CIN + 8 * g);
+                        b[dyi][n] = load8(wh + (tap * COUT + (nb0 + n) * 16 + r) * CIN + 8 * g);
                 }
             };
-            auto fetch_a = [&](int st) {
-                const int q = st / NR, ri = st % NR - 1;
+            auto fetch_a = [&](int q, int i) {
                 const int dz = q / 3 - 1, dx = q % 3 - 1;
-                return tile[lbase + ((dz * SY + ri) * NC + g) * SX + dx];
+                return tile[lbase + ((dz * SY + i - 1) * NC + g) * SX + dx];
             };
-            auto rows = [&](int st, const bf16x8 &a, const bf16x8 (&b)[3][NB]) {
-                const int ri = st % NR - 1;
-#pragma unroll
-                for (int dyi = 0; dyi < 3; ++dyi) {
-                    const int m = ri - (dyi - 1);   // output row fed with tap dy = dyi - 1
-                    if (m < 0 || m >= MBW) continue;
-#pragma unroll
-                    for (int n = 0; n < NB; ++n) acc[m][n] = mma(b[dyi][n], a, acc[m][n]);
-                }
-            };
-            bf16x8 bq[2][3][NB];
+            bf16x8 bq[2][3][NB], av[2];
             fetch_b(0, bq[0]);
-            bf16x8 a0 = fetch_a(0), a1;
+            av[0] = fetch_a(0, 0);
 #pragma unroll
-            for (int st = 0; st < NS; st += 2) {
-                const int q = st / NR;
-                if (st % NR == 0 && q + 1 < 9) fetch_b(q + 1, bq[(q + 1) & 1]);
-                a1 = fetch_a(st + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                rows(st, a0, bq[q & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (st + 2 < NS) a0 = fetch_a(st + 2);
-                __builtin_amdgcn_sched_barrier(0);
-                rows(st + 1, a1, bq[((st + 1) / NR) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
+            for (int q = 0; q < 9; ++q) {
+                if (q + 1 < 9) fetch_b(q + 1, bq[(q + 1) & 1]);
+#pragma unroll
+                for (int i = 0; i < NR; ++i) {
+                    if (i + 1 < NR)
+                        av[(i + 1) & 1] = fetch_a(q, i + 1);
+                    else if (q + 1 < 9)
+                        av[0] = fetch_a(q + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int dyi = 0; dyi < 3; ++dyi) {
+                        const int m = i - dyi;   // output row fed with tap dy = dyi - 1
+                        if (m < 0 || m >= MBW) continue;
+#pragma unroll
+                        for (int n = 0; n < NB; ++n)
+                            acc[m][n] = mma(bq[q & 1][dyi][n], av[i & 1], acc[m][n]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
         }
     }
@@ -521,12 +537,12 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
     }
 #pragma unroll
     for (int n = 0; n < NB; ++n) {
-        const int co0 = n * 16 + 4 * g;
+        const int co0 = (nb0 + n) * 16 + 4 * g;
         float bco[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) bco[j] = bias ? bias[co0 + j] : 0.0f;
-        // the block's destination (the same for the whole workgroup)
-        const bool second = n * 16 >= cat.nsplit;
+        // the block's destination (the same for the whole wave)
+        const bool second = (nb0 + n) * 16 >= cat.nsplit;
         void *dst = second ? cat.out2 : out;
         const int dcs = second ? cat.out2_cs : out_cs;
         const int dch = second ? cat.out2_off + co0 - cat.nsplit : out_off + co0;
