@@ -1187,11 +1187,24 @@ __global__ __launch_bounds__(256) void own_finish_kernel(const unsigned long lon
     const bool bad = !(cmax < __builtin_inf());
     const double inv = (cmax > 0.0 && !bad) ? ldexp(1.0, -own_kexp(cmax, g, cube_samples)) : 0.0;
     const size_t stride = static_cast<size_t>(gridDim.x) * 256;
-    for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += stride) {
+    size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+    auto put = [&](size_t j, unsigned long long a, float old) {
         const float v = bad ? __builtin_nanf("")
-                            : static_cast<float>(static_cast<double>(static_cast<long long>(acc64[i])) * inv);
-        vol[i] = accumulate ? vol[i] + v : v;
+                            : static_cast<float>(static_cast<double>(static_cast<long long>(a)) * inv);
+        vol[j] = accumulate ? old + v : v;
+    };
+    for (; i + 3 * stride < n; i += 4 * stride) {
+        unsigned long long a[4];
+        float old[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            a[k] = acc64[i + k * stride];
+            old[k] = accumulate ? vol[i + k * stride] : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) put(i + k * stride, a[k], old[k]);
     }
+    for (; i < n; i += stride) put(i, acc64[i], accumulate ? vol[i] : 0.0f);
 }
 
 BrickGrid plan_bricks(const RayGrid &g, int cap_chunks, bool own) {
@@ -1260,6 +1273,10 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
     const size_t shmem = 0;   // the brick is static LDS
     size_t fblocks = (nvol + 255) / 256;
     if (fblocks > 65536) fblocks = 65536;
+    // own_finish_kernel takes four voxels per pass and its workgroups stay: the
+    // exponent's logarithm is taken once per workgroup, not once per 256 voxels
+    // (256^3: 98 -> 35 us)
+    const size_t oblocks = std::min<size_t>((nvol + 1023) / 1024, 2048);
     // after the bricks: the direct form's chunk partials summed in chunk
     // order, or the owner form's integer volume scaled into vol
     auto finish = [&](int m) -> hipError_t {
@@ -1267,12 +1284,12 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
         if (e != hipSuccess) return e;
         if (!direct) {
             if (m == BP_ONES)
-                hipLaunchKernelGGL(own_finish_kernel<BP_ONES>, dim3(static_cast<unsigned>(fblocks)),
+                hipLaunchKernelGGL(own_finish_kernel<BP_ONES>, dim3(static_cast<unsigned>(oblocks)),
                                    dim3(256), 0, stream, bg.acc64, nvol, scratch, g,
                                    bg.cube_samples, scale, accumulate, vol);
             else
                 hipLaunchKernelGGL(own_finish_kernel<BP_PLAIN>,
-                                   dim3(static_cast<unsigned>(fblocks)), dim3(256), 0, stream,
+                                   dim3(static_cast<unsigned>(oblocks)), dim3(256), 0, stream,
                                    bg.acc64, nvol, scratch, g, bg.cube_samples, scale, accumulate,
                                    vol);
             return hipGetLastError();
