@@ -405,7 +405,7 @@ CTREX_API int ctrex_sirt_workspace_bytes_cyl(const ctrex_ctx *ctx, int32_t n_vie
  * Eq. (1) on the cylindrical domain: vol <- vol + alpha C B R (sino - A vol)
  * with A, B the cylinder operators above, R = 1 / (A 1), C = 1 / (B 1).
  * Arguments, the workspace and its weight cache, the attached scratch (here
- * the correction volume and the packed copy of vol, 20 bytes per voxel) and
+ * the correction volume and the packed copies of vol, 20 bytes per voxel) and
  * the residual norms as in ctrex_sirt_iterate; flags CTREX_NONNEG and
  * CTREX_RECOMPUTE_WEIGHTS only (the volume is FP32; no voxel weights).
  */

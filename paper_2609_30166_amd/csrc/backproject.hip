@@ -7,15 +7,20 @@
 // projection operator; Sec. 3.4: a projection's residual is spread over its
 // sub-views).
 //
+// Two forms share these ideas.  The default (bp_own_kernel) walks a sample only
+// in the brick that holds its lower corner and adds the bricks' integers into a
+// 64-bit volume; the direct form (bp_brick_kernel), for callers without room
+// for that volume, is described here:
+//
 // Scattering every sample to HBM would cost eight L2 float atomics per
-// sample.  Here a workgroup owns a brick of the volume (up to 32x15x16
+// sample.  A workgroup owns a brick of the volume (up to 32x15x16
 // voxels) held in LDS for a whole chunk of projections, accumulated as 64-bit
 // fixed point with LDS integer atomics: on gfx950 these sustain about twenty
 // times the lane rate of LDS FP32 atomic adds, and the sums are exact (so the
 // result does not depend on the order of the atomics).  A scale bounded from
 // max|r| puts the largest possible contribution at 2^30, so each one is a
-// 32-bit integer (weights formed in FP32, rounded to the nearest unit) while the 64-bit sums cannot overflow.  For every
-// (projection, sub-view) it bounds the detector pixels whose rays can reach
+// 32-bit integer (weights formed in FP32, rounded to the nearest unit) while
+// the 64-bit sums cannot overflow.  For every (projection, sub-view) it bounds the detector pixels whose rays can reach
 // the brick (the projection of the brick grown by one voxel and the warp
 // bound), redoes those rays' FP64 set-up, clips their sample range to the
 // grown brick, and adds its eight corners with LDS 64-bit integer atomics.
