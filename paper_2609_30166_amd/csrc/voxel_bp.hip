@@ -43,6 +43,9 @@ constexpr int VB_THREADS = VB_TX * VB_TY;
 constexpr int KZ1 = 8;                 // column of the kernel without footprints
 constexpr int FT_U = 49, FT_V = 36;    // largest footprint; an odd row stride
 constexpr int FT_N = VB_THREADS / 64;  // views per round, one per wave
+// Footprints are bounded in FP32, whose spacing is 1/128 below this pixel; one
+// further out is sampled from memory, where columns come from FP64.
+constexpr float FAR_PIXEL = 131072.0f;
 
 typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -333,7 +336,8 @@ vbp_tile_kernel(
             const double w = fma(M[8], bx, fma(M[9], by, fma(M[10], bz, M[11])));
             const unsigned long long pos = __ballot(w > 0.0), neg = __ballot(w < 0.0);
             const double r = 1.0 / w;
-            // 0.01 pixel covers the FP32 rounding here and of the samples
+            // 0.01 pixel covers the FP32 rounding here (two of 1/256 at most
+            // up to FAR_PIXEL) and of the samples' offsets within a column
             const float u = static_cast<float>(a * r), v = static_cast<float>(b * r);
             const float ua = floorf(min8(u) - 0.01f), ub = floorf(0.01f - min8(-u)) + 1.0f;
             const float va = floorf(min8(v) - 0.01f), vb = floorf(0.01f - min8(-v)) + 1.0f;
@@ -341,7 +345,8 @@ vbp_tile_kernel(
             // coefficient in the depth row; the corners bound the patch only
             // if it lies on one side of the source plane
             const bool fits = M[10] == 0.0 && (~pos == 0 || ~neg == 0) && ub - ua < FT_U &&
-                              vb - va < FT_V && fabsf(ua) < 8388608.0f && fabsf(va) < 8388608.0f;
+                              vb - va < FT_V && ua > -FAR_PIXEL && ub < FAR_PIXEL &&
+                              va > -FAR_PIXEL && vb < FAR_PIXEL;
             Footprint f{0, 0, 2, 0};
             if (fits) {   // uniform
                 f.u0 = __builtin_amdgcn_readfirstlane(static_cast<int>(ua));
