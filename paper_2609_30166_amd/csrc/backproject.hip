@@ -191,6 +191,13 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
     return x;
 }
 
+// First of the T samples of a wave that lane `lane` takes: floor(T lane / 64).
+// T reaches 2^30 (64 rays of under 2^24 samples, as ctrex_set_geometry
+// ensures), so the product itself does not fit 32 bits for steps below 1e-4.
+__device__ __forceinline__ int share(int T, int lane) {
+    return (T >> 6) * lane + (((T & 63) * lane) >> 6);
+}
+
 // One contribution as a 64-bit fixed-point integer: c (FP32, the scale
 // folded in, |c| < 2^31) rounded to the nearest integer, then sign-extended.
 // Rounding errs by at most half a unit and without bias, so the error of a
@@ -448,7 +455,7 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                     wave_sync();
                 }
                 // ---- lane takes samples [start, end) of the wave's T
-                const int start = (T * lane) >> 6, end = (T * (lane + 1)) >> 6;
+                const int start = share(T, lane), end = share(T, lane + 1);
                 int j = 0;   // last ray with S_j <= start: it owns sample `start`
 #pragma unroll
                 for (int st = 32; st > 0; st >>= 1) {
@@ -980,7 +987,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
                 wave_sync();
             }
             // ---- lane takes samples [start, end) of the wave's T
-            const int start = (T * lane) >> 6, end = (T * (lane + 1)) >> 6;
+            const int start = share(T, lane), end = share(T, lane + 1);
             int jr0 = 0;   // last ray with S_j <= start: it owns sample `start`
 #pragma unroll
             for (int st = 32; st > 0; st >>= 1) {
