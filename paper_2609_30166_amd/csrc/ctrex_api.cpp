@@ -115,26 +115,6 @@ int ctrex::ctx_scratch(ctrex_ctx *c, size_t bytes, void **out) {
 
 namespace {
 
-// Units of the projectors' launch (tile_coord): groups of up to 16 projections
-// (evened out, so that the last group is not mostly empty), runs of up to 32
-// tiles, shorter where there are too few blocks for 16 units per XCD.  Beyond
-// 2^23 blocks the padding of whole units could pass the 2^32 threads of a
-// launch: single pairs are handed out there.
-void set_launch_order(RayGrid &g) {
-    constexpr int kGroup = 16, kRun = 32, kUnits = 16 * N_XCD;
-    const long long tiles = static_cast<long long>(g.tiles_u) * g.tiles_v;
-    if (g.n_views <= 0 || g.total_blocks > (1 << 23)) {
-        g.grp = g.run = 1;
-        g.blocks = static_cast<unsigned>((g.total_blocks + N_XCD - 1) / N_XCD * N_XCD);
-        return;
-    }
-    const int groups = (g.n_views + kGroup - 1) / kGroup;
-    g.grp = (g.n_views + groups - 1) / groups;
-    g.run = std::max(1, std::min(kRun, g.total_blocks / (g.grp * kUnits)));
-    const long long units = (tiles + g.run - 1) / g.run * groups;
-    g.blocks = static_cast<unsigned>((units + N_XCD - 1) / N_XCD * N_XCD * g.grp * g.run);
-}
-
 RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views) {
     RayGrid g;
     g.tab = c->d_tab;
@@ -151,7 +131,10 @@ RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views)
     g.tiles_v = (c->n_v + TILE_V - 1) / TILE_V;
     const long long total = static_cast<long long>(g.tiles_u) * g.tiles_v * n_views;
     g.total_blocks = static_cast<int>(total);
-    set_launch_order(g);
+    const LaunchOrder o = launch_order(static_cast<long long>(g.tiles_u) * g.tiles_v, n_views);
+    g.grp = o.grp;
+    g.run = o.run;
+    g.blocks = static_cast<unsigned>(o.blocks);
     g.tube = c->fp_tube;
     return g;
 }

@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "launch_order.h"
+
 namespace ctrex {
 
 // Per sub-view geometry as the kernels read it (one 128-byte entry per
@@ -38,8 +40,8 @@ struct RayGrid {
     // detector tiling of the launch
     int tiles_u, tiles_v;
     int total_blocks;    // tiles_u * tiles_v * n_views
-    // launch order: units of grp projections x run tiles (tile_coord), and
-    // the workgroups of the launch (whole units, a multiple of N_XCD)
+    // launch order: units of grp projections x run tiles (pair_of), and the
+    // workgroups of the launch
     int grp, run;
     unsigned blocks;
     int tube = 0;        // forward projection of FP32 volumes through LDS-staged tubes
@@ -166,6 +168,5 @@ hipError_t launch_tv_grad(const float *x, int nx, int ny, int nz, float eps, flo
 constexpr int TILE_U = 16;
 constexpr int TILE_V = 16;
 constexpr int PROJ_THREADS = TILE_U * TILE_V;
-constexpr int N_XCD = 8;
 
 }  // namespace ctrex

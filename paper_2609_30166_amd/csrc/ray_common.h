@@ -344,15 +344,11 @@ struct TileCoord {
 // 32 x 8: 369).  A wave's lanes are 16 x 4 pixels.
 __device__ __forceinline__ TileCoord tile_coord(const RayGrid &g) {
     TileCoord t;
-    const int b = blockIdx.x, size = g.grp * g.run, tiles = g.tiles_u * g.tiles_v;
-    const int j = b / N_XCD, ul = j / size, in = j - ul * size;
-    const int unit = ul * N_XCD + b % N_XCD;
-    const int runs = (tiles + g.run - 1) / g.run;
-    const int gi = unit / runs, it = in / g.grp;
-    t.k = gi * g.grp + in - it * g.grp;
-    int tile = (unit - gi * runs) * g.run + it;
-    t.valid = t.k < g.n_views && tile < tiles;
-    if (!t.valid) t.k = tile = 0;
+    const Pair q = pair_of(static_cast<int>(blockIdx.x), g.grp, g.run, g.tiles_u * g.tiles_v,
+                           g.n_views);
+    t.k = q.k;
+    t.valid = q.valid;
+    const int tile = q.tile;
     t.lidx = tile * g.n_views + t.k;
     const int tu = tile % g.tiles_u;
     const int tv = tile / g.tiles_u;
