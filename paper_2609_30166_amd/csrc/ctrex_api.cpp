@@ -115,7 +115,33 @@ int ctrex::ctx_scratch(ctrex_ctx *c, size_t bytes, void **out) {
 
 namespace {
 
-RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views) {
+// True if the image of a box (half sides h, about the origin of the frame that
+// P acts on) covers at most a third of the detector's columns in every view, of
+// up to 64 spread over the m sub-views.
+bool narrow_image(const double *P, size_t m, const double h[3], int n_u) {
+    const size_t step = (m + 63) / 64;
+    for (size_t k = 0; k < m; k += step) {
+        const double *p = P + 12 * k;
+        double lo = n_u, hi = 0.0;
+        bool pos = true, neg = true;
+        for (int i = 0; i < 8; ++i) {
+            const double X = (i & 1) ? h[0] : -h[0], Y = (i & 2) ? h[1] : -h[1],
+                         Z = (i & 4) ? h[2] : -h[2];
+            const double w = p[8] * X + p[9] * Y + p[10] * Z + p[11];
+            const double u = (p[0] * X + p[1] * Y + p[2] * Z + p[3]) / w;
+            pos = pos && w > 0.0;
+            neg = neg && w < 0.0;
+            lo = std::min(lo, u);
+            hi = std::max(hi, u);
+        }
+        if (!(pos || neg) || !(std::min<double>(hi, n_u) - std::max(lo, 0.0) <= n_u / 3.0))
+            return false;
+    }
+    return true;
+}
+
+RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
+                  bool cyl = false) {
     RayGrid g;
     g.tab = c->d_tab;
     g.views = dev_views;
@@ -131,9 +157,12 @@ RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views)
     g.tiles_v = (c->n_v + TILE_V - 1) / TILE_V;
     const long long total = static_cast<long long>(g.tiles_u) * g.tiles_v * n_views;
     g.total_blocks = static_cast<int>(total);
-    const LaunchOrder o = launch_order(static_cast<long long>(g.tiles_u) * g.tiles_v, n_views);
+    const LaunchOrder o = launch_order(static_cast<long long>(g.tiles_u) * g.tiles_v, n_views,
+                                       (cyl ? c->cyl_narrow : c->narrow) ? g.tiles_u : 0);
     g.grp = o.grp;
     g.run = o.run;
+    g.runs = o.runs;
+    g.turn = o.turn;
     g.blocks = static_cast<unsigned>(o.blocks);
     g.tube = c->fp_tube;
     return g;
@@ -494,6 +523,7 @@ int ctrex_set_geometry(ctrex_ctx *c, const double *P, int32_t n_proj, int32_t n_
     }
     c->tab = std::move(tab);
     c->P_host.assign(P, P + 12 * m);
+    c->narrow = narrow_image(P, m, half, n_u);
     c->have_cyl = false;   // its tables derive from the view matrices
     c->n_proj = n_proj;
     c->n_sub = n_sub;
@@ -1079,7 +1109,7 @@ int check_cyl_ready(ctrex_ctx *c) {
 }
 
 RayGrid make_grid_cyl(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views) {
-    RayGrid g = make_grid(c, dev_views, n_views);
+    RayGrid g = make_grid(c, dev_views, n_views, true);
     g.tab = c->d_tab_cyl;
     g.nx = c->cyl_nr;
     g.ny = c->cyl_nphi;
@@ -1210,6 +1240,8 @@ int ctrex_set_cylinder(ctrex_ctx *c, int32_t n_r, int32_t n_phi, int32_t n_z, do
     }
     CTREX_HIP(c, hipMemcpy(c->d_tab_cyl, tab.data(), sizeof(SubView) * m, hipMemcpyHostToDevice));
     CTREX_HIP(c, hipMemcpy(c->d_P_cyl, Pc.data(), sizeof(double) * 12 * m, hipMemcpyHostToDevice));
+    const double box[3] = {rh, rh, hz};
+    c->cyl_narrow = narrow_image(Pc.data(), m, box, c->n_u);
     c->cyl_nr = n_r;
     c->cyl_nphi = n_phi;
     c->cyl_nz = n_z;

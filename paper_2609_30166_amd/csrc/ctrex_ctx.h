@@ -34,6 +34,8 @@ struct ctrex_ctx {
     double *d_P = nullptr;    // view matrices [n_proj * n_sub][12]
     size_t P_cap = 0;
     std::vector<double> P_host;  // the same, as set
+    // the volume's (the cylinder's) image is narrow (narrow_image)
+    bool narrow = false, cyl_narrow = false;
     // aligned cylindrical domain (ctrex_set_cylinder)
     bool have_cyl = false;
     int cyl_nr = 0, cyl_nphi = 0, cyl_nz = 0;

@@ -40,9 +40,8 @@ struct RayGrid {
     // detector tiling of the launch
     int tiles_u, tiles_v;
     int total_blocks;    // tiles_u * tiles_v * n_views
-    // launch order: units of grp projections x run tiles (pair_of), and the
-    // workgroups of the launch
-    int grp, run;
+    // launch order (LaunchOrder, pair_of) and the workgroups of the launch
+    int grp, run, runs, turn;
     unsigned blocks;
     int tube = 0;        // forward projection of FP32 volumes through LDS-staged tubes
 };

@@ -12,21 +12,36 @@ constexpr long long MAX_PROJ_BLOCKS = (1ll << 24) - 1;
 constexpr long long round_up_xcd(long long n) { return (n + N_XCD - 1) / N_XCD * N_XCD; }
 
 // Units of the projectors' launch (pair_of): groups of grp projections x runs
-// of run detector tiles, and the workgroups of whole units, a multiple of
-// N_XCD.
+// of run detector tiles (runs per group: runs), and the workgroups of whole
+// units, a multiple of N_XCD.  turn: see xcd_turn.
 struct LaunchOrder {
-    int grp = 1, run = 1;
+    int grp = 1, run = 1, runs = 1, turn = 0;
     long long blocks = 0;
 };
+
+// Turn of the j-th eight units against the XCDs: triangular numbers, so that
+// units at any fixed distance from one eight to the next, which may be all that
+// have work, go to all XCDs alike over 16 eights.
+constexpr unsigned xcd_turn(unsigned j) { return (j & 15) * ((j & 15) + 1) / 2; }
 
 // Groups of up to 16 projections, runs of up to 32 tiles, both evened out so
 // that the last one is not mostly empty; runs shorter where there are too few
 // pairs for 16 units per XCD.  Where the padding of whole units would exceed
 // the threads of a launch, single pairs are handed out.
-constexpr LaunchOrder launch_order(long long tiles, int n_views) {
+//
+// row (0, or the tiles of a detector row): the volume's image is much narrower
+// than the detector, so only a few tiles of each row have work.  Every second
+// or third unit then does, and where the units of a few rows are a multiple of
+// eight, all that do go to two or three XCDs.  Runs are whole rows there, each
+// with as much work as the next, and turned, since rows past the volume's ends
+// have none: 30 views of 384^2 of a 256 x 32 x 32 volume (z, y, x) 161 -> 95
+// us, of 300 x 60 x 60 324 -> 174; wider images keep the shorter runs (turned,
+// the SIRT step on a 96 x 603 x 192 cylinder took 7.4 ms instead of 6.5).
+constexpr LaunchOrder launch_order(long long tiles, int n_views, int row = 0) {
     constexpr int kGroup = 16, kRun = 32, kUnits = 16 * N_XCD;
     LaunchOrder o;
     const long long total = tiles * n_views;
+    o.runs = static_cast<int>(tiles);
     o.blocks = round_up_xcd(total);
     if (total <= 0 || total > MAX_PROJ_BLOCKS) return o;
     const int groups = (n_views + kGroup - 1) / kGroup;
@@ -35,12 +50,16 @@ constexpr LaunchOrder launch_order(long long tiles, int n_views) {
     if (run > kRun) run = kRun;
     if (run > tiles) run = tiles;
     if (run < 1) run = 1;
+    const bool rows = row > 0 && tiles / row * groups >= 2 * N_XCD;
+    if (rows) run = row;
     const long long runs = (tiles + run - 1) / run;
     run = (tiles + runs - 1) / runs;
     const long long blocks = round_up_xcd(runs * groups) * grp * run;
     if (blocks > MAX_PROJ_BLOCKS) return o;
     o.grp = grp;
     o.run = static_cast<int>(run);
+    o.runs = static_cast<int>(runs);
+    o.turn = rows ? 1 : 0;
     o.blocks = blocks;
     return o;
 }
@@ -52,16 +71,16 @@ struct Pair {
     bool valid;
 };
 
-constexpr Pair pair_of(int block, int grp, int run, int tiles, int n_views) {
-    const int size = grp * run;
-    const int j = block / N_XCD, ul = j / size, in = j - ul * size;
-    const int unit = ul * N_XCD + block % N_XCD;
-    const int runs = (tiles + run - 1) / run;
-    const int gi = unit / runs, it = in / grp;
-    const int k = gi * grp + in - it * grp;
-    const int tile = (unit - gi * runs) * run + it;
-    const bool valid = k < n_views && tile < tiles;
-    return Pair{valid ? k : 0, valid ? tile : 0, valid};
+constexpr Pair pair_of(unsigned block, int grp, int run, int runs, int turn, int tiles,
+                       int n_views) {
+    const unsigned size = static_cast<unsigned>(grp) * static_cast<unsigned>(run);
+    const unsigned j = block / N_XCD, ul = j / size, in = j - ul * size;
+    const unsigned unit = ul * N_XCD + (block + (turn ? xcd_turn(ul) : 0u)) % N_XCD;
+    const unsigned gi = unit / static_cast<unsigned>(runs), it = in / static_cast<unsigned>(grp);
+    const unsigned k = gi * static_cast<unsigned>(grp) + in - it * static_cast<unsigned>(grp);
+    const unsigned tile = (unit - gi * static_cast<unsigned>(runs)) * static_cast<unsigned>(run) + it;
+    const bool valid = k < static_cast<unsigned>(n_views) && tile < static_cast<unsigned>(tiles);
+    return Pair{valid ? static_cast<int>(k) : 0, valid ? static_cast<int>(tile) : 0, valid};
 }
 
 }  // namespace ctrex

@@ -344,7 +344,7 @@ struct TileCoord {
 // 32 x 8: 369).  A wave's lanes are 16 x 4 pixels.
 __device__ __forceinline__ TileCoord tile_coord(const RayGrid &g) {
     TileCoord t;
-    const Pair q = pair_of(static_cast<int>(blockIdx.x), g.grp, g.run, g.tiles_u * g.tiles_v,
+    const Pair q = pair_of(blockIdx.x, g.grp, g.run, g.runs, g.turn, g.tiles_u * g.tiles_v,
                            g.n_views);
     t.k = q.k;
     t.valid = q.valid;

@@ -9,8 +9,8 @@
 
 using namespace ctrex;
 
-static int check(long long tiles, int n_views, bool walk) {
-    const LaunchOrder o = launch_order(tiles, n_views);
+static int check(long long tiles, int n_views, bool walk, int row = 0) {
+    const LaunchOrder o = launch_order(tiles, n_views, row);
     const long long total = tiles * n_views;
     if (o.grp < 1 || o.run < 1 || o.run > tiles || o.blocks < total || o.blocks % N_XCD)
         return std::printf("%lld x %d: order %d %d %lld\n", tiles, n_views, o.grp, o.run, o.blocks);
@@ -20,11 +20,14 @@ static int check(long long tiles, int n_views, bool walk) {
     // (at most 1 / 112 of the pairs each where they hold several) fill whole XCDs
     if (o.blocks > 2 * total + total / 8 + N_XCD * o.grp * o.run)
         return std::printf("%lld x %d: %lld workgroups for %lld pairs\n", tiles, n_views, o.blocks, total);
+    if (row > 0 && o.run % row != 0 && tiles / row * n_views >= 1 << 9 && total < 1 << 22)
+        return std::printf("%lld x %d: runs of %d in rows of %d\n", tiles, n_views, o.run, row);
     if (!walk) return 0;
     std::vector<char> seen(total, 0);
     long long n = 0;
     for (long long b = 0; b < o.blocks; ++b) {
-        const Pair q = pair_of(static_cast<int>(b), o.grp, o.run, static_cast<int>(tiles), n_views);
+        const Pair q = pair_of(static_cast<unsigned>(b), o.grp, o.run, o.runs, o.turn,
+                               static_cast<int>(tiles), n_views);
         if (!q.valid) continue;
         if (q.k < 0 || q.k >= n_views || q.tile < 0 || q.tile >= tiles || seen[q.k * tiles + q.tile]++)
             return std::printf("%lld x %d: workgroup %lld takes (%d, %d)\n", tiles, n_views, b, q.k, q.tile);
@@ -33,12 +36,36 @@ static int check(long long tiles, int n_views, bool walk) {
     return n == total ? 0 : std::printf("%lld x %d: %lld of %lld pairs\n", tiles, n_views, n, total);
 }
 
+// Workgroups with work per XCD where the image covers two columns of tiles of
+// an n x n detector, without its first and last rows: at most a quarter above
+// the mean.
+static int balance(int n, int n_views) {
+    const LaunchOrder o = launch_order(1ll * n * n, n_views, n);
+    long long busy[N_XCD] = {}, all = 0, most = 0;
+    for (long long b = 0; b < o.blocks; ++b) {
+        const Pair q = pair_of(static_cast<unsigned>(b), o.grp, o.run, o.runs, o.turn, n * n, n_views);
+        const int u = q.tile % n, v = q.tile / n;
+        if (q.valid && (u == n / 2 || u == n / 2 - 1) && v > 1 && v < n - 2) ++busy[b % N_XCD], ++all;
+    }
+    for (long long x : busy) most = x > most ? x : most;
+    return 4 * N_XCD * most > 5 * all ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
+}
+
 int main() {
     const long long tiles[] = {1, 2, 3, 4, 9, 15, 16, 31, 32, 33, 63, 64, 65, 120, 576, 2304};
     const int views[] = {1, 2, 7, 8, 15, 16, 17, 31, 33, 60, 100, 255, 720, 1200, 5000, 65536};
     for (long long t : tiles)
         for (int v : views)
             if (check(t, v, t * v <= 2000000)) return 1;
+    // images of which a few columns are in use: runs of whole rows
+    const int rows[] = {1, 3, 12, 16, 24, 32, 48};
+    for (int row : rows)
+        for (int n : rows)
+            for (int v : views)
+                if (check(static_cast<long long>(row) * n, v, 1ll * row * n * v <= 2000000, row)) return 1;
+    for (int n : {12, 16, 24, 32, 40, 48})
+        for (int v : {30, 75, 180, 720})
+            if (balance(n, v)) return 1;
     // long lists of small images, up to the most that a launch holds
     for (long long t : tiles)
         for (long long v = 1 << 17; t * v < (1ll << 25); v += v / 3)
