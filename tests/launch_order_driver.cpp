@@ -37,8 +37,9 @@ static int check(long long tiles, int n_views, bool walk, int row = 0) {
 }
 
 // Workgroups with work per XCD where the image covers two columns of tiles of
-// an n x n detector, without its first and last rows: at most a quarter above
-// the mean.
+// an n x n detector, without its first and last rows: at most twice the mean
+// (small launches have 24 to 32 units, of which each XCD takes whole ones; units
+// at fixed distances put all work on two or three XCDs).
 static int balance(int n, int n_views) {
     const LaunchOrder o = launch_order(1ll * n * n, n_views, n);
     long long busy[N_XCD] = {}, all = 0, most = 0;
@@ -48,7 +49,7 @@ static int balance(int n, int n_views) {
         if (q.valid && (u == n / 2 || u == n / 2 - 1) && v > 1 && v < n - 2) ++busy[b % N_XCD], ++all;
     }
     for (long long x : busy) most = x > most ? x : most;
-    return 4 * N_XCD * most > 5 * all ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
+    return N_XCD * most > 2 * all ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
 }
 
 int main() {
