@@ -95,6 +95,7 @@ struct BrickGrid {
     int chunks;           // projection chunks per brick
     int views_per_chunk;
     int total;            // nbx * nby * nbz * chunks
+    int run, turn;        // owner form: launch order (BrickOrder)
     int accumulate;       // add into vol (else overwrite; needs chunks == 1)
     float wscale;         // every contribution is multiplied by this factor
     double cube_samples;  // max samples of one ray inside a side-2 cube
@@ -755,15 +756,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
     __shared__ float nodes[WARP ? 3 * OWN_NODES : 1];
     RayRec *const tabw = rays + (threadIdx.x & ~63);
     const int lane = threadIdx.x & 63;
-    // ---- block -> (brick, projection chunk): rows of bricks go to the XCDs
-    // in turn, so that they stay equally loaded where the ends of the volume
-    // see few rays
-    const int per_row = bg.nbx * bg.chunks;
-    const int j = blockIdx.x / N_XCD, jr = j / per_row;
-    const int row = jr * N_XCD + blockIdx.x % N_XCD;
-    if (row >= bg.nby * bg.nbz) return;
-    const int jx = j - jr * per_row;
-    const int ibx = jx / bg.chunks, chunk = jx - ibx * bg.chunks;
+    // ---- block -> (brick, projection chunk)
+    const unsigned item = item_of(blockIdx.x, bg.run, bg.turn);
+    if (item >= static_cast<unsigned>(bg.total)) return;
+    const int br = static_cast<int>(item / static_cast<unsigned>(bg.chunks));
+    const int chunk = static_cast<int>(item) - br * bg.chunks;
+    const int row = br / bg.nbx, ibx = br - row * bg.nbx;
     const int ibz = row / bg.nby, iby = row - ibz * bg.nby;
     const int x0 = ibx * bg.bx, y0 = iby * bg.by, z0 = ibz * bg.bz;
     const int ex = min(bg.bx, g.nx - x0), ey = min(bg.by, g.ny - y0), ez = min(bg.bz, g.nz - z0);
@@ -1240,6 +1238,8 @@ BrickGrid plan_bricks(const RayGrid &g, int cap_chunks, bool own) {
     // h >= step / 2 whenever a ray has two samples, and a side-2 cube holds a
     // chord of at most 2 sqrt(3)
     bg.cube_samples = floor(4.0 * 1.7320508075688772 / g.step) + 1.0;
+    bg.run = 1;
+    bg.turn = 0;
     bg.partials = nullptr;
     bg.acc64 = nullptr;
     bg.accumulate = 0;
@@ -1279,9 +1279,10 @@ hipError_t launch_back(const RayGrid &g, const WarpGrid &w, const double *Pmat, 
     const dim3 grid(static_cast<unsigned>(per * N_XCD));
     const dim3 block(static_cast<unsigned>(wp ? bp_threads<true>() : bp_threads<false>()));
     const bool nodes_fit = wp && !direct && brick_nodes_fit(w, g, bg);
-    // owner form: whole rows of bricks, a multiple of N_XCD rows
-    const int rows = (bg.nby * bg.nbz + N_XCD - 1) / N_XCD * N_XCD;
-    const dim3 own_grid(static_cast<unsigned>(rows) * bg.nbx * bg.chunks);
+    const BrickOrder order = brick_order(bg.nby * bg.nbz, bg.nbx, bg.chunks);
+    bg.run = order.run;
+    bg.turn = order.turn;
+    const dim3 own_grid(static_cast<unsigned>(order.blocks));
     const size_t shmem = 0;   // the brick is static LDS
     size_t fblocks = (nvol + 255) / 256;
     if (fblocks > 65536) fblocks = 65536;

@@ -1,7 +1,7 @@
-// Checks the projectors' launch order on the CPU: every (projection, tile)
-// pair taken by exactly one workgroup, with bounded padding, and no launch
-// beyond 2^32 threads that the pairs alone would fit.  Ends with 1 and a
-// message at the first failure.
+// Checks the launch orders on the CPU: every (projection, tile) pair and every
+// (brick, chunk) item taken by exactly one workgroup, with bounded padding, no
+// launch beyond 2^32 threads that the work alone would fit, and no XCD with
+// much more than the others.  Ends with 1 and a message at the first failure.
 #include <cstdio>
 #include <vector>
 
@@ -52,7 +52,35 @@ static int balance(int n, int n_views) {
     return N_XCD * most > 2 * all ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
 }
 
+// The backprojector's items: each taken once, and no XCD with more than a unit
+// above the mean.
+static int bricks(int rows, int per_row, int chunks) {
+    const BrickOrder o = brick_order(rows, per_row, chunks);
+    const long long total = 1ll * rows * per_row * chunks;
+    if (o.run < 1 || o.blocks < total || o.blocks % N_XCD || o.blocks > total + N_XCD * o.run)
+        return std::printf("bricks %d x %d x %d: %d %lld\n", rows, per_row, chunks, o.run, o.blocks);
+    std::vector<char> seen(total, 0);
+    long long busy[N_XCD] = {}, n = 0, most = 0;
+    for (long long b = 0; b < o.blocks; ++b) {
+        const unsigned i = item_of(static_cast<unsigned>(b), o.run, o.turn);
+        if (i >= total) continue;
+        if (seen[i]++) return std::printf("bricks %d x %d x %d: item %u twice\n", rows, per_row, chunks, i);
+        ++n, ++busy[b % N_XCD];
+    }
+    for (long long x : busy) most = x > most ? x : most;
+    if (n != total || (most - o.run) * N_XCD > total)
+        return std::printf("bricks %d x %d x %d: %lld taken, %lld on one XCD\n", rows, per_row, chunks, n, most);
+    // an XCD takes whole units: an eighth more than the mean from 64 units on
+    if (total >= 64 && 8 * N_XCD * most > 9 * total + 8 * N_XCD)
+        return std::printf("bricks %d x %d x %d: %lld on one XCD\n", rows, per_row, chunks, most);
+    return 0;
+}
+
 int main() {
+    for (int rows : {1, 2, 4, 7, 8, 9, 16, 25, 26, 49, 72, 100, 169, 256, 1024})
+        for (int per_row : {1, 2, 3, 4, 8, 16})
+            for (int chunks : {1, 2, 3, 8, 15, 25, 45, 250})
+                if (bricks(rows, per_row, chunks)) return 1;
     const long long tiles[] = {1, 2, 3, 4, 9, 15, 16, 31, 32, 33, 63, 64, 65, 120, 576, 2304};
     const int views[] = {1, 2, 7, 8, 15, 16, 17, 31, 33, 60, 100, 255, 720, 1200, 5000, 65536};
     for (long long t : tiles)
