@@ -168,6 +168,13 @@ RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
     return g;
 }
 
+// The Cartesian grid of the voxel-driven backprojector.
+VoxelGrid box_voxels(const ctrex_ctx *c) {
+    VoxelGrid v;
+    v.foot_kz = c->foot_kz;
+    return v;
+}
+
 WarpGrid make_warp(const ctrex_ctx *c) {
     WarpGrid w;
     w.U = c->d_U;
@@ -524,6 +531,7 @@ int ctrex_set_geometry(ctrex_ctx *c, const double *P, int32_t n_proj, int32_t n_
     c->tab = std::move(tab);
     c->P_host.assign(P, P + 12 * m);
     c->narrow = narrow_image(P, m, half, n_u);
+    c->foot_kz = footprint_column(P, m, VoxelGrid{}, nx, ny, nz);
     c->have_cyl = false;   // its tables derive from the view matrices
     c->n_proj = n_proj;
     c->n_sub = n_sub;
@@ -797,7 +805,7 @@ int ctrex_back_project_voxel(ctrex_ctx *c, const void *sino, int32_t sino_dtype,
         return CTREX_OK;
     }
     CTREX_HIP(c, launch_back_voxel(make_grid(c, dv, nv), c->d_P, sino, sino_dtype, vol,
-                                   accumulate ? 1 : 0, 0, VoxelGrid{}, s));
+                                   accumulate ? 1 : 0, 0, box_voxels(c), s));
     return CTREX_OK;
 }
 
@@ -889,7 +897,7 @@ int ctrex_sirt_iterate(ctrex_ctx *c, float *vol, const void *sino, int32_t sino_
         FpExtra none{nullptr, nullptr, nullptr};
         CTREX_HIP(c, launch_forward(g, w, nullptr, F32, Rw, F32, FP_RECIP_ONES, none, s));
         if (vbp)
-            CTREX_HIP(c, launch_back_voxel(g, c->d_P, nullptr, F32, Cw, 0, 1, VoxelGrid{}, s));
+            CTREX_HIP(c, launch_back_voxel(g, c->d_P, nullptr, F32, Cw, 0, 1, box_voxels(c), s));
         else
             CTREX_HIP(c, launch_back(g, w, c->d_P, nullptr, F32, Cw, 0, BP_ONES, c->d_scalar, part,
                                      s));
@@ -921,7 +929,7 @@ int ctrex_sirt_iterate(ctrex_ctx *c, float *vol, const void *sino, int32_t sino_
         CTREX_HIP(c, launch_sum_partials(partials, g.total_blocks, resid + (k % kResidCap), s));
         CTREX_HIP(c, t_bp.begin());
         if (vbp)
-            CTREX_HIP(c, launch_back_voxel(g, c->d_P, r, rdt, z, 0, 0, VoxelGrid{}, s));
+            CTREX_HIP(c, launch_back_voxel(g, c->d_P, r, rdt, z, 0, 0, box_voxels(c), s));
         else
             CTREX_HIP(c, launch_back(g, w, c->d_P, r, rdt, z, 0, BP_PLAIN, c->d_scalar, part, s));
         CTREX_HIP(c, t_bp.end());
@@ -1126,6 +1134,7 @@ VoxelGrid cyl_voxels(const ctrex_ctx *c) {
     v.cyl = 1;
     v.dr = c->cyl_dr;
     v.dz = c->cyl_dz;
+    v.foot_kz = c->cyl_foot_kz;
     return v;
 }
 
@@ -1242,6 +1251,7 @@ int ctrex_set_cylinder(ctrex_ctx *c, int32_t n_r, int32_t n_phi, int32_t n_z, do
     CTREX_HIP(c, hipMemcpy(c->d_P_cyl, Pc.data(), sizeof(double) * 12 * m, hipMemcpyHostToDevice));
     const double box[3] = {rh, rh, hz};
     c->cyl_narrow = narrow_image(Pc.data(), m, box, c->n_u);
+    c->cyl_foot_kz = footprint_column(Pc.data(), m, VoxelGrid{1, dr, dz}, n_r, n_phi, n_z);
     c->cyl_nr = n_r;
     c->cyl_nphi = n_phi;
     c->cyl_nz = n_z;

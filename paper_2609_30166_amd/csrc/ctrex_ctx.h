@@ -36,6 +36,7 @@ struct ctrex_ctx {
     std::vector<double> P_host;  // the same, as set
     // the volume's (the cylinder's) image is narrow (narrow_image)
     bool narrow = false, cyl_narrow = false;
+    int foot_kz = 0, cyl_foot_kz = 0;   // footprint_column
     // aligned cylindrical domain (ctrex_set_cylinder)
     bool have_cyl = false;
     int cyl_nr = 0, cyl_nphi = 0, cyl_nz = 0;

@@ -110,7 +110,13 @@ size_t back_scratch_bytes(const RayGrid &g, int max_chunks = 0, bool direct = fa
 struct VoxelGrid {
     int cyl = 0;
     double dr = 1.0, dz = 1.0;
+    int foot_kz = 0;   // footprint_column of this geometry
 };
+
+// Voxels per column with which the voxel-driven backprojector copies detector
+// footprints to LDS, or 0 if most do not fit there: judged from 5 patches of the
+// volume in up to 64 of the m sub-views P.  Either way the results agree.
+int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz);
 
 // vol (+)= B sino with the voxel-driven backprojector (ones != 0: B 1, sino
 // ignored); deterministic, no scratch.  Needs n_u, n_v >= 2.

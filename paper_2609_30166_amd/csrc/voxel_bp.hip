@@ -30,9 +30,13 @@
 // with a path of 13 instructions per voxel for columns inside the image: 6.2).
 // Four waves per SIMD: at 3 (no spills) 4.2 ms, at 5 (spills) 14.  A view
 // whose footprint does not fit, or whose depth row has a z coefficient, is
-// sampled from global memory with the border handling.
+// sampled from global memory with the border handling; geometries in which more
+// than a third are take vbp_kernel, which does nothing else (footprint_column).
 
 #include "ray_common.h"
+
+#include <algorithm>
+#include <cmath>
 
 namespace ctrex {
 namespace {
@@ -40,7 +44,6 @@ namespace {
 constexpr int VB_TX = 16;
 constexpr int VB_TY = 16;
 constexpr int VB_THREADS = VB_TX * VB_TY;
-constexpr int KZ1 = 8;                 // column of the kernel without footprints
 constexpr int FT_U = 49, FT_V = 36;    // largest footprint; an odd row stride
 constexpr int FT_N = VB_THREADS / 64;  // views per round, one per wave
 // Footprints are bounded in FP32, whose spacing is 1/128 below this pixel; one
@@ -119,7 +122,7 @@ struct Column {
     int kn;
 };
 
-__device__ __forceinline__ Column column_of(const VoxelGrid &vg, int ix, int iy, int z0, int ny,
+__host__ __device__ __forceinline__ Column column_of(const VoxelGrid &vg, int ix, int iy, int z0, int ny,
                                             int nx, int nz, int kz) {
     Column c;
     c.kn = min(kz, nz - z0);
@@ -140,6 +143,36 @@ __device__ __forceinline__ Column column_of(const VoxelGrid &vg, int ix, int iy,
         c.sz = 1.0;
     }
     return c;
+}
+
+// Box around the (x, y) positions of a patch's voxel centres.
+struct PatchBox {
+    double xa, xb, ya, yb;
+};
+
+__host__ __device__ __forceinline__ PatchBox patch_box(const VoxelGrid &vg, int tx, int ty, int nx,
+                                                       int ny, int nz) {
+    const int x1 = min(tx * VB_TX + VB_TX - 1, nx - 1), y1 = min(ty * VB_TY + VB_TY - 1, ny - 1);
+    const Column c0 = column_of(vg, tx * VB_TX, ty * VB_TY, 0, ny, nx, nz, 1);
+    const Column c1 = column_of(vg, x1, ty * VB_TY, 0, ny, nx, nz, 1);
+    const Column c2 = column_of(vg, tx * VB_TX, y1, 0, ny, nx, nz, 1);
+    const Column c3 = column_of(vg, x1, y1, 0, ny, nx, nz, 1);
+    PatchBox b;
+    b.xa = fmin(fmin(c0.X, c1.X), fmin(c2.X, c3.X));
+    b.xb = fmax(fmax(c0.X, c1.X), fmax(c2.X, c3.X));
+    b.ya = fmin(fmin(c0.Y, c1.Y), fmin(c2.Y, c3.Y));
+    b.yb = fmax(fmax(c0.Y, c1.Y), fmax(c2.Y, c3.Y));
+    if (vg.cyl) {
+        // the outer arc bulges past its chord by r (1 - cos(half angle))
+        const double r = (x1 + 0.5) * vg.dr;
+        const double half = 3.14159265358979323846 * (y1 - ty * VB_TY) / ny;
+        const double e = half < 1.5707963 ? r * (1.0 - cos(half)) + 1e-9 * r : 2.0 * r;
+        b.xa -= e;
+        b.xb += e;
+        b.ya -= e;
+        b.yb += e;
+    }
+    return b;
 }
 
 // acc[k] += the samples of one sub-view's image at the column's voxels.
@@ -218,11 +251,13 @@ __device__ __forceinline__ void store_column(const double (&acc)[KZ], int n_sub,
     }
 }
 
-// B 1 (no image to read): every view through add_view.
-__global__ __launch_bounds__(VB_THREADS) void vbp_ones_kernel(
+// Every view through add_view, without barriers or LDS: B 1 (ONES: no image to
+// read), and geometries whose views mostly have no footprint.
+template <typename TS, bool ONES, int KZ>
+__global__ __launch_bounds__(VB_THREADS) void vbp_kernel(
     const double *__restrict__ Pm, const int *__restrict__ views, int n_views, int n_sub, int nu,
-    int nv, int nx, int ny, int nz, int tiles_y, int tiles_z, float *__restrict__ vol,
-    int accumulate, VoxelGrid vg) {
+    int nv, int nx, int ny, int nz, int tiles_y, int tiles_z, const TS *__restrict__ sino,
+    float *__restrict__ vol, int accumulate, VoxelGrid vg) {
     int t = xcd_tile(blockIdx.x, gridDim.x);
     const int tz = t % tiles_z;
     t /= tiles_z;
@@ -231,18 +266,20 @@ __global__ __launch_bounds__(VB_THREADS) void vbp_ones_kernel(
     const int ix = tx * VB_TX + (threadIdx.x & (VB_TX - 1));
     const int iy = ty * VB_TY + (threadIdx.x / VB_TX);
     if (ix >= nx || iy >= ny) return;  // no barriers below
-    const int z0 = tz * KZ1;
-    const Column c = column_of(vg, ix, iy, z0, ny, nx, nz, KZ1);
-    double acc[KZ1];
+    const int z0 = tz * KZ;
+    const Column c = column_of(vg, ix, iy, z0, ny, nx, nz, KZ);
+    const size_t img_px = static_cast<size_t>(nu) * nv;
+    double acc[KZ];
 #pragma unroll
-    for (int k = 0; k < KZ1; ++k) acc[k] = 0.0;
+    for (int k = 0; k < KZ; ++k) acc[k] = 0.0;
     for (int j = 0; j < n_views; ++j) {
         const int p = views ? views[j] : j;
+        const TS *img = ONES ? nullptr : sino + j * img_px;
         for (int s = 0; s < n_sub; ++s)
-            add_view<float, true, KZ1>(c, Pm + 12 * (static_cast<size_t>(p) * n_sub + s), nullptr,
-                                       nu, nv, acc);
+            add_view<TS, ONES, KZ>(c, Pm + 12 * (static_cast<size_t>(p) * n_sub + s), img, nu, nv,
+                                   acc);
     }
-    store_column<KZ1>(acc, n_sub, c.kn, ix, iy, z0, nx, ny, accumulate, vol);
+    store_column<KZ>(acc, n_sub, c.kn, ix, iy, z0, nx, ny, accumulate, vol);
 }
 
 // Minimum over each group of 8 consecutive lanes.
@@ -293,31 +330,10 @@ vbp_tile_kernel(
     const int lane = threadIdx.x & 63;
     // corner (lane & 7) of a box around the patch's voxel centres, over the
     // columns' full KZ voxels
-    double bx, by, bz;
-    {
-        const int x1 = min(tx * VB_TX + VB_TX - 1, nx - 1), y1 = min(ty * VB_TY + VB_TY - 1, ny - 1);
-        const Column c0 = column_of(vg, tx * VB_TX, ty * VB_TY, z0, ny, nx, nz, KZ);
-        const Column c1 = column_of(vg, x1, ty * VB_TY, z0, ny, nx, nz, KZ);
-        const Column c2 = column_of(vg, tx * VB_TX, y1, z0, ny, nx, nz, KZ);
-        const Column c3 = column_of(vg, x1, y1, z0, ny, nx, nz, KZ);
-        double xa = fmin(fmin(c0.X, c1.X), fmin(c2.X, c3.X));
-        double xb = fmax(fmax(c0.X, c1.X), fmax(c2.X, c3.X));
-        double ya = fmin(fmin(c0.Y, c1.Y), fmin(c2.Y, c3.Y));
-        double yb = fmax(fmax(c0.Y, c1.Y), fmax(c2.Y, c3.Y));
-        if (vg.cyl) {
-            // the outer arc bulges past its chord by r (1 - cos(half angle))
-            const double r = (x1 + 0.5) * vg.dr;
-            const double half = 3.14159265358979323846 * (y1 - ty * VB_TY) / ny;
-            const double e = half < 1.5707963 ? r * (1.0 - cos(half)) + 1e-9 * r : 2.0 * r;
-            xa -= e;
-            xb += e;
-            ya -= e;
-            yb += e;
-        }
-        bx = (lane & 1) ? xb : xa;
-        by = (lane & 2) ? yb : ya;
-        bz = c.Z0 + ((lane & 4) ? (KZ - 1) * c.sz : 0.0);
-    }
+    const PatchBox pb = patch_box(vg, tx, ty, nx, ny, nz);
+    const double bx = (lane & 1) ? pb.xb : pb.xa;
+    const double by = (lane & 2) ? pb.yb : pb.ya;
+    const double bz = c.Z0 + ((lane & 4) ? (KZ - 1) * c.sz : 0.0);
     const size_t img_px = static_cast<size_t>(nu) * nv;
     const int n_pairs = n_views * n_sub;
     double acc[KZ];
@@ -440,53 +456,103 @@ vbp_tile_kernel(
     if (gx < nx && gy < ny) store_column<KZ>(acc, n_sub, c.kn, ix, iy, z0, nx, ny, accumulate, vol);
 }
 
-template <typename TS, int KZ>
-hipError_t launch_tile(const RayGrid &g, const double *Pm, const TS *src, float *vol,
-                       int accumulate, const VoxelGrid &vg, hipStream_t s) {
-    const int tiles_x = (g.nx + VB_TX - 1) / VB_TX;
-    const int tiles_y = (g.ny + VB_TY - 1) / VB_TY;
-    const int tiles_z = (g.nz + KZ - 1) / KZ;
-    const long long n_tiles = static_cast<long long>(tiles_x) * tiles_y * tiles_z;
-    if (n_tiles <= 0 || n_tiles >= (1ll << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((vbp_tile_kernel<TS, KZ>), dim3(static_cast<unsigned>(n_tiles)),
-                       dim3(VB_THREADS), 0, s, Pm, g.views, g.n_views, g.n_sub, g.n_u, g.n_v, g.nx,
-                       g.ny, g.nz, tiles_y, tiles_z, src, vol, accumulate, vg);
-    return hipGetLastError();
-}
-
 // The longest column that still gives 400 workgroups (a column's FP64
 // projection and a patch's footprint are shared by its voxels; fewer workgroups
 // leave CUs idle).  60 views of (1.5 n)^2 at n^3, columns of 16 / 8 / 4: n = 64
 // 97 / 73 / 55 us (64 / 128 / 256 workgroups), 96: 106 / 90 / 95, 128: 126 /
 // 132 / 180, 200: 369 / 435 / 625 us.
-template <typename TS>
-hipError_t launch_typed(const RayGrid &g, const double *Pm, const void *sino, float *vol,
-                        int accumulate, const VoxelGrid &vg, hipStream_t s) {
+int column_length(int nx, int ny, int nz) {
     constexpr long long FILL = 400;
-    const TS *src = static_cast<const TS *>(sino);
-    const long long patches = static_cast<long long>((g.nx + VB_TX - 1) / VB_TX) *
-                              ((g.ny + VB_TY - 1) / VB_TY);
-    if (patches * ((g.nz + 15) / 16) >= FILL)
-        return launch_tile<TS, 16>(g, Pm, src, vol, accumulate, vg, s);
-    if (patches * ((g.nz + 7) / 8) >= FILL)
-        return launch_tile<TS, 8>(g, Pm, src, vol, accumulate, vg, s);
-    return launch_tile<TS, 4>(g, Pm, src, vol, accumulate, vg, s);
+    const long long patches = static_cast<long long>((nx + VB_TX - 1) / VB_TX) *
+                              ((ny + VB_TY - 1) / VB_TY);
+    if (patches * ((nz + 15) / 16) >= FILL) return 16;
+    return patches * ((nz + 7) / 8) >= FILL ? 8 : 4;
 }
 
-hipError_t launch_ones(const RayGrid &g, const double *Pm, float *vol, int accumulate,
-                       const VoxelGrid &vg, hipStream_t s) {
+// FOOT: with footprints.
+template <typename TS, int KZ, bool FOOT, bool ONES = false>
+hipError_t launch_columns(const RayGrid &g, const double *Pm, const TS *src, float *vol,
+                          int accumulate, const VoxelGrid &vg, hipStream_t s) {
     const int tiles_x = (g.nx + VB_TX - 1) / VB_TX;
     const int tiles_y = (g.ny + VB_TY - 1) / VB_TY;
-    const int tiles_z = (g.nz + KZ1 - 1) / KZ1;
+    const int tiles_z = (g.nz + KZ - 1) / KZ;
     const long long n_tiles = static_cast<long long>(tiles_x) * tiles_y * tiles_z;
     if (n_tiles <= 0 || n_tiles >= (1ll << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(vbp_ones_kernel, dim3(static_cast<unsigned>(n_tiles)), dim3(VB_THREADS), 0,
-                       s, Pm, g.views, g.n_views, g.n_sub, g.n_u, g.n_v, g.nx, g.ny, g.nz, tiles_y,
-                       tiles_z, vol, accumulate, vg);
+    const dim3 grid(static_cast<unsigned>(n_tiles)), block(VB_THREADS);
+    if constexpr (FOOT)
+        hipLaunchKernelGGL((vbp_tile_kernel<TS, KZ>), grid, block, 0, s, Pm, g.views, g.n_views,
+                           g.n_sub, g.n_u, g.n_v, g.nx, g.ny, g.nz, tiles_y, tiles_z, src, vol,
+                           accumulate, vg);
+    else
+        hipLaunchKernelGGL((vbp_kernel<TS, ONES, KZ>), grid, block, 0, s, Pm, g.views, g.n_views,
+                           g.n_sub, g.n_u, g.n_v, g.nx, g.ny, g.nz, tiles_y, tiles_z, src, vol,
+                           accumulate, vg);
     return hipGetLastError();
 }
 
+template <typename TS>
+hipError_t launch_typed(const RayGrid &g, const double *Pm, const void *sino, float *vol,
+                        int accumulate, const VoxelGrid &vg, hipStream_t s) {
+    const TS *src = static_cast<const TS *>(sino);
+    const int kz = static_cast<long long>(g.n_views) * g.n_sub < 2 ? 0 : vg.foot_kz;
+    if (kz == 16) return launch_columns<TS, 16, true>(g, Pm, src, vol, accumulate, vg, s);
+    if (kz == 8) return launch_columns<TS, 8, true>(g, Pm, src, vol, accumulate, vg, s);
+    if (kz == 4) return launch_columns<TS, 4, true>(g, Pm, src, vol, accumulate, vg, s);
+    return column_length(g.nx, g.ny, g.nz) >= 8
+               ? launch_columns<TS, 8, false>(g, Pm, src, vol, accumulate, vg, s)
+               : launch_columns<TS, 4, false>(g, Pm, src, vol, accumulate, vg, s);
+}
+
+// Whether a view's footprint of the patch (tx, ty), kz voxels about the middle
+// of the volume, fits in LDS (vbp_tile_kernel's rule).
+bool footprint_fits(const double *M, const VoxelGrid &vg, int tx, int ty, int nx, int ny, int nz,
+                    int kz) {
+    if (M[10] != 0.0) return false;
+    const PatchBox b = patch_box(vg, tx, ty, nx, ny, nz);
+    const double dz = vg.cyl ? vg.dz : 1.0, hz = 0.5 * (kz - 1) * dz;
+    double u0 = FAR_PIXEL, u1 = -FAR_PIXEL, v0 = FAR_PIXEL, v1 = -FAR_PIXEL;
+    bool pos = true, neg = true;
+    for (int i = 0; i < 8; ++i) {
+        const double x = (i & 1) ? b.xb : b.xa, y = (i & 2) ? b.yb : b.ya, z = (i & 4) ? hz : -hz;
+        const double w = M[8] * x + M[9] * y + M[11];
+        const double u = (M[0] * x + M[1] * y + M[2] * z + M[3]) / w;
+        const double v = (M[4] * x + M[5] * y + M[6] * z + M[7]) / w;
+        pos = pos && w > 0.0;
+        neg = neg && w < 0.0;
+        u0 = std::min(u0, u);
+        u1 = std::max(u1, u);
+        v0 = std::min(v0, v);
+        v1 = std::max(v1, v);
+    }
+    return (pos || neg) && u0 > -FAR_PIXEL && u1 < FAR_PIXEL && v0 > -FAR_PIXEL &&
+           v1 < FAR_PIXEL && std::floor(u1) + 1.0 - std::floor(u0) < FT_U &&
+           std::floor(v1) + 1.0 - std::floor(v0) < FT_V;
+}
+
 }  // namespace
+
+// With a footprint a view costs vbp_tile_kernel half of what it costs
+// vbp_kernel, without one up to twice as much, so up to a third of them may lack
+// it.  60 views of 384^2 at 256^3, vbp_tile_kernel and vbp_kernel: 606 and 1218
+// us with footprints, jittered (none has one) 2609 and 2070, of 768^2 (footprints
+// too large) 1927 and 1252; 2 x 512 x 512 (z, y, x) jittered 139 and 100.  A
+// single view has too few loads in flight (256^3: 36 and 31 us).
+int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz) {
+    const int lx = (nx - 1) / VB_TX, ly = (ny - 1) / VB_TY;
+    const int at[5][2] = {{lx / 2, ly / 2}, {0, 0}, {lx, 0}, {0, ly}, {lx, ly}};
+    const size_t step = (m + 63) / 64;
+    const int longest = column_length(nx, ny, nz);
+    for (int kz = longest; kz >= std::min(longest, 8); kz /= 2) {
+        size_t all = 0, miss = 0;
+        for (size_t k = 0; k < m; k += step)
+            for (const auto &t : at) {
+                ++all;
+                miss += !footprint_fits(P + 12 * k, vg, t[0], t[1], nx, ny, nz, kz);
+            }
+        if (3 * miss <= all) return kz;
+    }
+    return 0;
+}
 
 hipError_t launch_back_voxel(const RayGrid &g, const double *Pm, const void *sino, int sino_dtype,
                              float *vol, int accumulate, int ones, const VoxelGrid &vg,
@@ -495,7 +561,8 @@ hipError_t launch_back_voxel(const RayGrid &g, const double *Pm, const void *sin
     if (g.n_u < 2 || g.n_v < 2 || g.n_u >= (1 << 24) || g.n_v >= (1 << 24) ||
         static_cast<long long>(g.n_u) * g.n_v >= (1ll << 30))
         return hipErrorInvalidValue;
-    if (ones) return launch_ones(g, Pm, vol, accumulate, vg, s);
+    if (ones)
+        return launch_columns<float, 8, false, true>(g, Pm, nullptr, vol, accumulate, vg, s);
     switch (sino_dtype) {
     case F32: return launch_typed<float>(g, Pm, sino, vol, accumulate, vg, s);
     case BF16: return launch_typed<bf16_t>(g, Pm, sino, vol, accumulate, vg, s);
