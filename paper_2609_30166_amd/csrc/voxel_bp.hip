@@ -36,6 +36,7 @@
 #include "ray_common.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 namespace ctrex {
@@ -458,15 +459,28 @@ vbp_tile_kernel(
 
 // The longest column that still gives 400 workgroups (a column's FP64
 // projection and a patch's footprint are shared by its voxels; fewer workgroups
-// leave CUs idle).  60 views of (1.5 n)^2 at n^3, columns of 16 / 8 / 4: n = 64
+// leave CUs idle), 60 views of (1.5 n)^2 at n^3, columns of 16 / 8 / 4: n = 64
 // 97 / 73 / 55 us (64 / 128 / 256 workgroups), 96: 106 / 90 / 95, 128: 126 /
-// 132 / 180, 200: 369 / 435 / 625 us.
-int column_length(int nx, int ny, int nz) {
+// 132 / 180, 200: 369 / 435 / 625 us.  Voxels past the volume's end cost what
+// others do, so a shorter column is taken where it is cheaper in all, a column
+// costing its voxels and `extra` more: four, or eight with upright detectors
+// (M[2] = 0), whose voxels are cheaper.  Columns of 16 and 8, 20 x 512 x 512 (z,
+// y, x): upright 293 and 303 us, rolled 346 and 226 (314 from memory).
+int column_length(int nx, int ny, int nz, int extra) {
     constexpr long long FILL = 400;
     const long long patches = static_cast<long long>((nx + VB_TX - 1) / VB_TX) *
                               ((ny + VB_TY - 1) / VB_TY);
-    if (patches * ((nz + 15) / 16) >= FILL) return 16;
-    return patches * ((nz + 7) / 8) >= FILL ? 8 : 4;
+    int best = 4;
+    long long least = LLONG_MAX;
+    for (int kz = 16; kz >= 4; kz /= 2) {
+        const long long columns = (nz + kz - 1) / kz;
+        if (kz > 4 && patches * columns < FILL) continue;
+        if (columns * (kz + extra) < least) {
+            least = columns * (kz + extra);
+            best = kz;
+        }
+    }
+    return best;
 }
 
 // FOOT: with footprints.
@@ -498,7 +512,7 @@ hipError_t launch_typed(const RayGrid &g, const double *Pm, const void *sino, fl
     if (kz == 16) return launch_columns<TS, 16, true>(g, Pm, src, vol, accumulate, vg, s);
     if (kz == 8) return launch_columns<TS, 8, true>(g, Pm, src, vol, accumulate, vg, s);
     if (kz == 4) return launch_columns<TS, 4, true>(g, Pm, src, vol, accumulate, vg, s);
-    return column_length(g.nx, g.ny, g.nz) >= 8
+    return column_length(g.nx, g.ny, g.nz, 4) >= 8
                ? launch_columns<TS, 8, false>(g, Pm, src, vol, accumulate, vg, s)
                : launch_columns<TS, 4, false>(g, Pm, src, vol, accumulate, vg, s);
 }
@@ -541,7 +555,9 @@ int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int
     const int lx = (nx - 1) / VB_TX, ly = (ny - 1) / VB_TY;
     const int at[5][2] = {{lx / 2, ly / 2}, {0, 0}, {lx, 0}, {0, ly}, {lx, ly}};
     const size_t step = (m + 63) / 64;
-    const int longest = column_length(nx, ny, nz);
+    bool upright = true;
+    for (size_t k = 0; k < m; k += step) upright = upright && P[12 * k + 2] == 0.0;
+    const int longest = column_length(nx, ny, nz, upright ? 8 : 4);
     for (int kz = longest; kz >= std::min(longest, 8); kz /= 2) {
         size_t all = 0, miss = 0;
         for (size_t k = 0; k < m; k += step)

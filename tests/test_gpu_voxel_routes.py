@@ -58,3 +58,13 @@ def test_some_views_without_a_footprint(shape, views):
     zoom[:2, 2] = -1.5 * np.array([N_U - 1.0, N_V - 1.0])
     P[7] = zoom @ P[7]
     _check(P, shape, views)
+
+
+@pytest.mark.parametrize("roll", [0.0, 3.0])
+@pytest.mark.parametrize("n_z", [2, 5, 8, 20, 25])
+def test_thin_volumes(n_z, roll):
+    """Columns shortened to the volume's height, upright and rolled detectors."""
+    shape = (n_z, 330, 310)
+    a = np.radians(roll)
+    R = np.array([[np.cos(a), -np.sin(a), 3.0], [np.sin(a), np.cos(a), -2.0], [0, 0, 1.0]])
+    _check(R @ _orbit(shape), shape)
