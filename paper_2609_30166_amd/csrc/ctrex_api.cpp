@@ -141,7 +141,7 @@ bool narrow_image(const double *P, size_t m, const double h[3], int n_u) {
 }
 
 RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
-                  bool cyl = false) {
+                  bool cyl = false, int group = 0) {
     RayGrid g;
     g.tab = c->d_tab;
     g.views = dev_views;
@@ -158,7 +158,7 @@ RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
     const long long total = static_cast<long long>(g.tiles_u) * g.tiles_v * n_views;
     g.total_blocks = static_cast<int>(total);
     const LaunchOrder o = launch_order(static_cast<long long>(g.tiles_u) * g.tiles_v, n_views,
-                                       (cyl ? c->cyl_narrow : c->narrow) ? g.tiles_u : 0);
+                                       (cyl ? c->cyl_narrow : c->narrow) ? g.tiles_u : 0, group);
     g.grp = o.grp;
     g.run = o.run;
     g.runs = o.runs;
@@ -1116,8 +1116,10 @@ int check_cyl_ready(ctrex_ctx *c) {
     return CTREX_OK;
 }
 
-RayGrid make_grid_cyl(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views) {
-    RayGrid g = make_grid(c, dev_views, n_views, true);
+RayGrid make_grid_cyl(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
+                      int vol_dtype = F32) {
+    RayGrid g = make_grid(c, dev_views, n_views, true,
+                          cyl_view_group(c->cyl_nr, c->cyl_nphi, c->cyl_nz, vol_dtype));
     g.tab = c->d_tab_cyl;
     g.nx = c->cyl_nr;
     g.ny = c->cyl_nphi;
@@ -1284,7 +1286,7 @@ int ctrex_forward_project_cyl(ctrex_ctx *c, const void *vol, int32_t vol_dtype, 
         if ((st = ctx_scratch(c, CL.total, &scr))) return st;
         if ((st = make_polar_copies(c, static_cast<const float *>(vol), scr, ex, s))) return st;
     }
-    CTREX_HIP(c, launch_forward_cyl(make_grid_cyl(c, dv, nv), cyl_of(c), vol, vol_dtype, sino,
+    CTREX_HIP(c, launch_forward_cyl(make_grid_cyl(c, dv, nv, vol_dtype), cyl_of(c), vol, vol_dtype, sino,
                                     sino_dtype, FP_PLAIN, ex, s));
     return CTREX_OK;
 }

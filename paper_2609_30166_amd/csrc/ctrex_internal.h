@@ -134,6 +134,10 @@ struct CylGrid {
     double rh2, hz;                           // hull radius^2 and half height
 };
 CylGrid make_cyl_grid(int nr, int nphi, int nz, double dr, double dz);
+// Most views to a group of the launch order (launch_order) for projecting a
+// polar volume: all of them (INT_MAX) if it is a 16-bit one larger than an XCD's
+// 4 MB L2, else the default (0).
+int cyl_view_group(int nr, int nphi, int nz, int vol_dtype);
 hipError_t launch_forward_cyl(const RayGrid &g, const CylGrid &c, const void *vol, int vol_dtype,
                               void *out, int out_dtype, int mode, const FpExtra &ex,
                               hipStream_t stream);

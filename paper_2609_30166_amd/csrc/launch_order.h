@@ -25,7 +25,7 @@ struct LaunchOrder {
 // have work, go to all XCDs alike over 16 eights.
 constexpr unsigned xcd_turn(unsigned j) { return (j & 15) * ((j & 15) + 1) / 2; }
 
-// Groups of up to 16 projections, runs of up to 32 tiles, both evened out so
+// Groups of up to `group` projections (0: 16), runs of up to 32 tiles, both evened out so
 // that the last one is not mostly empty; runs shorter where there are too few
 // pairs for 16 units per XCD.  Where the padding of whole units would exceed
 // the threads of a launch, single pairs are handed out.
@@ -38,16 +38,17 @@ constexpr unsigned xcd_turn(unsigned j) { return (j & 15) * ((j & 15) + 1) / 2; 
 // have none: 30 views of 384^2 of a 256 x 32 x 32 volume (z, y, x) 161 -> 95
 // us, of 300 x 60 x 60 324 -> 174; wider images keep the shorter runs (turned,
 // the SIRT step on a 96 x 603 x 192 cylinder took 7.4 ms instead of 6.5).
-constexpr LaunchOrder launch_order(long long tiles, int n_views, int row = 0) {
+constexpr LaunchOrder launch_order(long long tiles, int n_views, int row = 0, int group = 0) {
     constexpr int kGroup = 16, kRun = 32, kUnits = 16 * N_XCD;
     LaunchOrder o;
     const long long total = tiles * n_views;
     o.runs = static_cast<int>(tiles);
     o.blocks = round_up_xcd(total);
     if (total <= 0 || total > MAX_PROJ_BLOCKS) return o;
-    const int groups = (n_views + kGroup - 1) / kGroup;
+    if (group <= 0) group = kGroup;
+    const int groups = (n_views - 1) / group + 1;
     const int grp = (n_views + groups - 1) / groups;
-    long long run = total / (grp * kUnits);
+    long long run = total / (static_cast<long long>(grp) * kUnits);
     if (run > kRun) run = kRun;
     if (run > tiles) run = tiles;
     if (run < 1) run = 1;

@@ -2,6 +2,7 @@
 // (brick, chunk) item taken by exactly one workgroup, with bounded padding, no
 // launch beyond 2^32 threads that the work alone would fit, and no XCD with
 // much more than the others.  Ends with 1 and a message at the first failure.
+#include <climits>
 #include <cstdio>
 #include <vector>
 
@@ -9,8 +10,8 @@
 
 using namespace ctrex;
 
-static int check(long long tiles, int n_views, bool walk, int row = 0) {
-    const LaunchOrder o = launch_order(tiles, n_views, row);
+static int check(long long tiles, int n_views, bool walk, int row = 0, int group = 0) {
+    const LaunchOrder o = launch_order(tiles, n_views, row, group);
     const long long total = tiles * n_views;
     if (o.grp < 1 || o.run < 1 || o.run > tiles || o.blocks < total || o.blocks % N_XCD)
         return std::printf("%lld x %d: order %d %d %lld\n", tiles, n_views, o.grp, o.run, o.blocks);
@@ -85,7 +86,7 @@ int main() {
     const int views[] = {1, 2, 7, 8, 15, 16, 17, 31, 33, 60, 100, 255, 720, 1200, 5000, 65536};
     for (long long t : tiles)
         for (int v : views)
-            if (check(t, v, t * v <= 2000000)) return 1;
+            if (check(t, v, t * v <= 2000000) || check(t, v, t * v <= 200000, 0, INT_MAX)) return 1;
     // images of which a few columns are in use: runs of whole rows
     const int rows[] = {1, 3, 12, 16, 24, 32, 48};
     for (int row : rows)
