@@ -286,12 +286,7 @@ void fp_cyl_kernel(RayGrid g, CylGrid c,
                                                               TS *__restrict__ out, FpExtra ex) {
     TileCoord t = tile_coord(g);
     if (!t.valid) return;  // uniform over the block
-    if constexpr (BIG) {
-        // 8 x 8 pixels per wave instead of 16 x 4
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        t.iu += (wave & 1) * 8 + (lane & 7) - (lane & 15);
-        t.iv += (wave >> 1) * 8 + (lane >> 3) - (wave * 4 + (lane >> 4));
-    }
+    if constexpr (BIG) t = square_waves(t);
     const bool active = t.iu < g.n_u && t.iv < g.n_v;
     float y = 0.0f;
     if (active) y = cyl_march<TV, MODE>(g, c, vol, ex, t);

@@ -393,8 +393,9 @@ __global__ __launch_bounds__(PROJ_THREADS) __attribute__((amdgpu_waves_per_eu(1,
 void fp_kernel(RayGrid g, WarpGrid w,
                                                           const TV *__restrict__ vol,
                                                           TS *__restrict__ out, FpExtra ex) {
-    const TileCoord t = tile_coord(g);
+    TileCoord t = tile_coord(g);
     if (!t.valid) return;  // uniform over the block
+    if constexpr (TUBE) t = square_waves(t);
     const VolDims d = vol_dims(g);
     const bool active = t.iu < g.n_u && t.iv < g.n_v;
     if constexpr (TUBE) {

@@ -360,6 +360,14 @@ __device__ __forceinline__ TileCoord tile_coord(const RayGrid &g) {
     return t;
 }
 
+// The same with 8 x 8 pixels to a wave.
+__device__ __forceinline__ TileCoord square_waves(TileCoord t) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    t.iu += (wave & 1) * 8 + (lane & 7) - (lane & 15);
+    t.iv += (wave >> 1) * 8 + (lane >> 3) - (wave * 4 + (lane >> 4));
+    return t;
+}
+
 __device__ __forceinline__ VolDims vol_dims(const RayGrid &g) {
     VolDims d;
     d.nx = g.nx;
