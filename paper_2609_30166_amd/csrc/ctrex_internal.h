@@ -114,7 +114,7 @@ struct VoxelGrid {
 };
 
 // Voxels per column with which the voxel-driven backprojector copies detector
-// footprints to LDS, or 0 if most do not fit there: judged from 5 patches of the
+// footprints to LDS, or 0 if most do not fit there: judged from 9 patches of the
 // volume in up to 64 of the m sub-views P.  Either way the results agree.
 int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz);
 

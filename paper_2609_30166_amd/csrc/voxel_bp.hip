@@ -31,7 +31,7 @@
 // Four waves per SIMD: at 3 (no spills) 4.2 ms, at 5 (spills) 14.  A view
 // whose footprint does not fit, or whose depth row has a z coefficient, is
 // sampled from global memory with the border handling; geometries in which more
-// than a third are take vbp_kernel, which does nothing else (footprint_column).
+// than a tenth are take vbp_kernel, which does nothing else (footprint_column).
 
 #include "ray_common.h"
 
@@ -546,14 +546,17 @@ bool footprint_fits(const double *M, const VoxelGrid &vg, int tx, int ty, int nx
 }  // namespace
 
 // With a footprint a view costs vbp_tile_kernel half of what it costs
-// vbp_kernel, without one up to twice as much, so up to a third of them may lack
-// it.  60 views of 384^2 at 256^3, vbp_tile_kernel and vbp_kernel: 606 and 1218
-// us with footprints, jittered (none has one) 2609 and 2070, of 768^2 (footprints
-// too large) 1927 and 1252; 2 x 512 x 512 (z, y, x) jittered 139 and 100.  A
-// single view has too few loads in flight (256^3: 36 and 31 us).
+// vbp_kernel, without one one and a half to twice as much, and patches that lack
+// many hold the launch up: up to a tenth may lack it.  60 views of 384^2 at
+// 256^3, vbp_tile_kernel and vbp_kernel: 606 and 1218 us with footprints,
+// jittered (none has one) 2609 and 2070, of 768^2 (too large) 1927 and 1252;
+// 2 x 512 x 512 (z, y, x) jittered 139 and 100; cylinder of 150 x 400 x 100, of
+// whose outer patches half lack it, 744 and 506, 150 x 500 x 100 (a sixth) 723
+// and 649, 100 x 400 x 150 (a twentieth) 416 and 506.  A single view has too few
+// loads in flight (256^3: 36 and 31 us).
 int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz) {
-    const int lx = (nx - 1) / VB_TX, ly = (ny - 1) / VB_TY;
-    const int at[5][2] = {{lx / 2, ly / 2}, {0, 0}, {lx, 0}, {0, ly}, {lx, ly}};
+    // the middle patches of a division into 3 x 3
+    const int px = (nx - 1) / VB_TX + 1, py = (ny - 1) / VB_TY + 1;
     const size_t step = (m + 63) / 64;
     bool upright = true;
     for (size_t k = 0; k < m; k += step) upright = upright && P[12 * k + 2] == 0.0;
@@ -561,11 +564,12 @@ int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int
     for (int kz = longest; kz >= std::min(longest, 8); kz /= 2) {
         size_t all = 0, miss = 0;
         for (size_t k = 0; k < m; k += step)
-            for (const auto &t : at) {
+            for (int i = 0; i < 9; ++i) {
                 ++all;
-                miss += !footprint_fits(P + 12 * k, vg, t[0], t[1], nx, ny, nz, kz);
+                miss += !footprint_fits(P + 12 * k, vg, (2 * (i % 3) + 1) * px / 6,
+                                        (2 * (i / 3) + 1) * py / 6, nx, ny, nz, kz);
             }
-        if (3 * miss <= all) return kz;
+        if (10 * miss <= all) return kz;
     }
     return 0;
 }

@@ -68,3 +68,19 @@ def test_thin_volumes(n_z, roll):
     a = np.radians(roll)
     R = np.array([[np.cos(a), -np.sin(a), 3.0], [np.sin(a), np.cos(a), -2.0], [0, 0, 1.0]])
     _check(R @ _orbit(shape), shape)
+
+
+@pytest.mark.parametrize("views", [[4], [4, 4, 4, 0, 7, 7], [8, 2, 5, 3], [39, 4, 7, 1, 20, 4, 12]])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_few_views_without_a_footprint(shape, views):
+    """Two of 40 views lack a footprint, too few to leave footprints out."""
+    ext, n_proj = float(max(shape)), 40
+    P = synth.circular_cone(n_proj, N_U, N_V, 3.0 * ext, 6.0 * ext, 2.4 * ext / N_U).copy()
+    P[4] = _tilt(P[4], 5.0)
+    zoom = np.diag([4.0, 4.0, 1.0])
+    zoom[:2, 2] = -1.5 * np.array([N_U - 1.0, N_V - 1.0])
+    P[7] = zoom @ P[7]
+    s = np.random.default_rng(4).normal(0.5, 1.0, (len(views), N_V, N_U)).astype(np.float32)
+    z = Geometry(P, N_U, N_V, shape).back_voxel(torch.from_numpy(s).cuda(), views=views)
+    ref = oracle.back_voxel(P, shape, N_U, N_V, s.astype(np.float64), views=views)
+    assert np.linalg.norm(z.cpu().numpy() - ref) <= 1e-5 * np.linalg.norm(ref)
