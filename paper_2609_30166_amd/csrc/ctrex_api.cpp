@@ -157,8 +157,8 @@ RayGrid make_grid(const ctrex_ctx *c, const int32_t *dev_views, int32_t n_views,
     g.tiles_v = (c->n_v + TILE_V - 1) / TILE_V;
     const long long total = static_cast<long long>(g.tiles_u) * g.tiles_v * n_views;
     g.total_blocks = static_cast<int>(total);
-    const LaunchOrder o = launch_order(static_cast<long long>(g.tiles_u) * g.tiles_v, n_views,
-                                       (cyl ? c->cyl_narrow : c->narrow) ? g.tiles_u : 0, group);
+    const LaunchOrder o = launch_order(g.tiles_u, g.tiles_v, n_views,
+                                       cyl ? c->cyl_narrow : c->narrow, group, cyl);
     g.grp = o.grp;
     g.run = o.run;
     g.runs = o.runs;

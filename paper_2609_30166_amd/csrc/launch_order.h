@@ -25,23 +25,35 @@ struct LaunchOrder {
 // have work, go to all XCDs alike over 16 eights.
 constexpr unsigned xcd_turn(unsigned j) { return (j & 15) * ((j & 15) + 1) / 2; }
 
-// Groups of up to `group` projections (0: 16), runs of up to 32 tiles, both evened out so
-// that the last one is not mostly empty; runs shorter where there are too few
-// pairs for 16 units per XCD.  Where the padding of whole units would exceed
-// the threads of a launch, single pairs are handed out.
+constexpr long long gcd(long long a, long long b) { return b == 0 ? a : gcd(b, a % b); }
+
+// Order for n_views images of rows x row tiles: groups of up to `group`
+// projections (0: 16), runs of up to 32 tiles, both evened out so that the last
+// one is not mostly empty; runs shorter where there are too few pairs for 16
+// units per XCD.  Where the padding of whole units would exceed the threads of a
+// launch, single pairs are handed out.
 //
-// row (0, or the tiles of a detector row): the volume's image is much narrower
-// than the detector, so only a few tiles of each row have work.  Every second
-// or third unit then does, and where the units of a few rows are a multiple of
-// eight, all that do go to two or three XCDs.  Runs are whole rows there, each
-// with as much work as the next, and turned, since rows past the volume's ends
-// have none: 30 views of 384^2 of a 256 x 32 x 32 volume (z, y, x) 161 -> 95
-// us, of 300 x 60 x 60 324 -> 174; wider images keep the shorter runs (turned,
-// the SIRT step on a 96 x 603 x 192 cylinder took 7.4 ms instead of 6.5).
-constexpr LaunchOrder launch_order(long long tiles, int n_views, int row = 0, int group = 0) {
-    constexpr int kGroup = 16, kRun = 32, kUnits = 16 * N_XCD;
+// narrow: the volume's image is much narrower than the detector, so only a few
+// tiles of each row have work.  Every second or third unit then does, and where
+// the units of a few rows are a multiple of eight, all that do go to two or
+// three XCDs.  Runs are whole rows there, each with as much work as the next,
+// and turned, since rows past the volume's ends have none: 30 views of 384^2 of
+// a 256 x 32 x 32 volume (z, y, x) 161 -> 95 us, of 300 x 60 x 60 324 -> 174.
+//
+// Wider images are turned only if units come back to the same XCDs after one to
+// three rows of at least eight (cyl, the cylindrical domain, whose rays differ
+// more in length: one to four rows, and half of all rows at most) and not all of
+// them run at once, three to a CU: some XCDs would have the detector's middle,
+// others its sides, where rays are short.  30
+// views at 80^3 (8 tiles to a row) 129 -> 114 us, 165^3 (16) 722 -> 598, 256^3
+// (24, runs of 9) 2779 -> 2327.  Others keep the same columns on an XCD for
+// longer (turned, 100^3 with 30 views took 181 us instead of 171, the SIRT step
+// on a 96 x 603 x 192 cylinder 7.4 ms instead of 6.5).
+constexpr LaunchOrder launch_order(int row, int rows, int n_views, bool narrow = false,
+                                   int group = 0, bool cyl = false) {
+    constexpr int kGroup = 16, kRun = 32, kUnits = 16 * N_XCD, kRound = 3 * 256;
     LaunchOrder o;
-    const long long total = tiles * n_views;
+    const long long tiles = static_cast<long long>(row) * rows, total = tiles * n_views;
     o.runs = static_cast<int>(tiles);
     o.blocks = round_up_xcd(total);
     if (total <= 0 || total > MAX_PROJ_BLOCKS) return o;
@@ -52,16 +64,19 @@ constexpr LaunchOrder launch_order(long long tiles, int n_views, int row = 0, in
     if (run > kRun) run = kRun;
     if (run > tiles) run = tiles;
     if (run < 1) run = 1;
-    const bool rows = row > 0 && tiles / row * groups >= 2 * N_XCD;
-    if (rows) run = row;
+    narrow = narrow && static_cast<long long>(rows) * groups >= 2 * N_XCD;
+    if (narrow) run = row;
     const long long runs = (tiles + run - 1) / run;
     run = (tiles + runs - 1) / runs;
     const long long blocks = round_up_xcd(runs * groups) * grp * run;
     if (blocks > MAX_PROJ_BLOCKS) return o;
+    // rows after which units fall on the same XCDs again
+    const long long period = N_XCD * run / gcd(row, N_XCD * run);
+    const int limit = cyl ? (rows < 8 ? rows / 2 : 4) : rows < 8 ? 0 : 3;
     o.grp = grp;
     o.run = static_cast<int>(run);
     o.runs = static_cast<int>(runs);
-    o.turn = rows ? 1 : 0;
+    o.turn = narrow || (period <= limit && group == kGroup && total > kRound) ? 1 : 0;
     o.blocks = blocks;
     return o;
 }

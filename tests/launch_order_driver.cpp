@@ -10,19 +10,17 @@
 
 using namespace ctrex;
 
-static int check(long long tiles, int n_views, bool walk, int row = 0, int group = 0) {
-    const LaunchOrder o = launch_order(tiles, n_views, row, group);
-    const long long total = tiles * n_views;
+static int check(int row, int rows, int n_views, bool walk, bool narrow = false, int group = 0) {
+    const LaunchOrder o = launch_order(row, rows, n_views, narrow, group);
+    const long long tiles = 1ll * row * rows, total = tiles * n_views;
     if (o.grp < 1 || o.run < 1 || o.run > tiles || o.blocks < total || o.blocks % N_XCD)
         return std::printf("%lld x %d: order %d %d %lld\n", tiles, n_views, o.grp, o.run, o.blocks);
     if (total <= MAX_PROJ_BLOCKS - N_XCD && o.blocks > MAX_PROJ_BLOCKS)
         return std::printf("%lld x %d: %lld workgroups\n", tiles, n_views, o.blocks);
     // runs and groups are evened out to under twice their items, and units
-    // (at most 1 / 112 of the pairs each where they hold several) fill whole XCDs
+    // fill whole XCDs
     if (o.blocks > 2 * total + total / 8 + N_XCD * o.grp * o.run)
         return std::printf("%lld x %d: %lld workgroups for %lld pairs\n", tiles, n_views, o.blocks, total);
-    if (row > 0 && o.run % row != 0 && tiles / row * n_views >= 1 << 9 && total < 1 << 22)
-        return std::printf("%lld x %d: runs of %d in rows of %d\n", tiles, n_views, o.run, row);
     if (!walk) return 0;
     std::vector<char> seen(total, 0);
     long long n = 0;
@@ -37,20 +35,23 @@ static int check(long long tiles, int n_views, bool walk, int row = 0, int group
     return n == total ? 0 : std::printf("%lld x %d: %lld of %lld pairs\n", tiles, n_views, n, total);
 }
 
-// Workgroups with work per XCD where the image covers two columns of tiles of
-// an n x n detector, without its first and last rows: at most twice the mean
-// (small launches have 24 to 32 units, of which each XCD takes whole ones; units
-// at fixed distances put all work on two or three XCDs).
-static int balance(int n, int n_views) {
-    const LaunchOrder o = launch_order(1ll * n * n, n_views, n);
+// Work per XCD of an n x n detector whose middle columns (two of them, narrow,
+// or half) have all of it, without its first and last rows: less than twice the
+// mean, or twice the mean if narrow (small launches have 24 to 32 units, of which
+// each XCD takes whole ones; units at fixed distances put all work on two or
+// three XCDs, or on half of them).
+static int balance(int n, int n_views, bool narrow, bool cyl) {
+    const LaunchOrder o = launch_order(n, n, n_views, narrow, 0, cyl);
+    const int half = narrow ? 1 : n / 4;
     long long busy[N_XCD] = {}, all = 0, most = 0;
     for (long long b = 0; b < o.blocks; ++b) {
         const Pair q = pair_of(static_cast<unsigned>(b), o.grp, o.run, o.runs, o.turn, n * n, n_views);
         const int u = q.tile % n, v = q.tile / n;
-        if (q.valid && (u == n / 2 || u == n / 2 - 1) && v > 1 && v < n - 2) ++busy[b % N_XCD], ++all;
+        if (q.valid && u >= n / 2 - half && u < n / 2 + half && v > 1 && v < n - 2)
+            ++busy[b % N_XCD], ++all;
     }
     for (long long x : busy) most = x > most ? x : most;
-    return N_XCD * most > 2 * all ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
+    return N_XCD * most > (narrow ? 2 * all : 2 * all - 1) ? std::printf("%d^2 x %d: %lld of %lld\n", n, n_views, most, all) : 0;
 }
 
 // The backprojector's items: each taken once, and no XCD with more than a unit
@@ -82,24 +83,24 @@ int main() {
         for (int per_row : {1, 2, 3, 4, 8, 16})
             for (int chunks : {1, 2, 3, 8, 15, 25, 45, 250})
                 if (bricks(rows, per_row, chunks)) return 1;
-    const long long tiles[] = {1, 2, 3, 4, 9, 15, 16, 31, 32, 33, 63, 64, 65, 120, 576, 2304};
+    const int sides[][2] = {{1, 1}, {2, 1}, {1, 3}, {2, 2}, {3, 3}, {15, 1}, {4, 4}, {31, 1}, {8, 4}, {33, 1},
+                            {8, 8}, {5, 13}, {12, 10}, {16, 16}, {24, 24}, {48, 48}, {24, 2}, {1, 40}};
     const int views[] = {1, 2, 7, 8, 15, 16, 17, 31, 33, 60, 100, 255, 720, 1200, 5000, 65536};
-    for (long long t : tiles)
-        for (int v : views)
-            if (check(t, v, t * v <= 2000000) || check(t, v, t * v <= 200000, 0, INT_MAX)) return 1;
-    // images of which a few columns are in use: runs of whole rows
-    const int rows[] = {1, 3, 12, 16, 24, 32, 48};
-    for (int row : rows)
-        for (int n : rows)
-            for (int v : views)
-                if (check(static_cast<long long>(row) * n, v, 1ll * row * n * v <= 2000000, row)) return 1;
-    for (int n : {12, 16, 24, 32, 40, 48})
+    for (const auto &s : sides)
+        for (int v : views) {
+            const long long total = 1ll * s[0] * s[1] * v;
+            if (check(s[0], s[1], v, total <= 2000000) || check(s[0], s[1], v, total <= 200000, true) ||
+                check(s[0], s[1], v, total <= 200000, false, INT_MAX))
+                return 1;
+        }
+    for (int n : {8, 12, 16, 24, 32, 40, 48})
         for (int v : {30, 75, 180, 720})
-            if (balance(n, v)) return 1;
+            if (balance(n, v, false, false) || balance(n, v, false, true) || (n > 8 && balance(n, v, true, false)))
+                return 1;
     // long lists of small images, up to the most that a launch holds
-    for (long long t : tiles)
-        for (long long v = 1 << 17; t * v < (1ll << 25); v += v / 3)
-            if (check(t, static_cast<int>(v), false)) return 1;
+    for (const auto &s : sides)
+        for (long long v = 1 << 17; s[0] * s[1] * v < (1ll << 25); v += v / 3)
+            if (check(s[0], s[1], static_cast<int>(v), false)) return 1;
     std::puts("ok");
     return 0;
 }
