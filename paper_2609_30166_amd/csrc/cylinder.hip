@@ -267,13 +267,14 @@ __device__ __forceinline__ float cyl_march(const RayGrid &g, const CylGrid &c,
 // 12.40, 13.01).  The ray-length mode (no gathers) keeps the default.
 //
 // 16-bit volumes have no copies, so most samples of a wave lie on lines of
-// their own, and one beyond an XCD's L2 (BIG) lives from the few rays in flight
-// sharing them: 2 waves per SIMD, 8 x 8 pixels per wave, and a tile's views one
-// after the other (cyl_view_group).  120 views of 288^2, 96 x 603 x 192:
-// 11.6 -> 9.2 ms (9.8 with the arc tangent of the library), without the cap
-// 10.8, without the square pixels 10.2, by 16 views 9.2; 384^2, 128 x 800 x 256,
-// 30 views: 11.6 -> 7.5 ms, 8.2, 7.4 and 10.6.  Smaller volumes keep the default
-// (20 x 40 x 200: 202 us, with all of this 275).
+// their own; its rays are 8 x 8 pixels there (40 x 250 x 80, 30 / 120 views of
+// 120^2: 193 / 615 us, with 16 x 4 pixels 214 / 660; 48 x 300 x 96, 60 views 605
+// and 615, but 32 x 200 x 64 229 and 205).  A volume beyond an XCD's L2 (BIG)
+// lives from the few rays in flight sharing lines: 2 waves per SIMD and a tile's
+// views one after the other (cyl_view_group).  60 views of 288^2, 96 x 603 x 192:
+// 4.66 ms, without the cap 5.42, by 16 views 4.86, with neither 5.73; 128 x 800 x
+// 256, 60 views of 384^2: 14.7 ms, 15.5, 17.8 and 18.5.  Smaller volumes keep the
+// default (20 x 40 x 200: 197 us, with both 275).
 template <typename TV, int MODE, bool BIG>
 constexpr int fp_cyl_max_waves() {
     return MODE == FP_RECIP_ONES ? 8 : sizeof(TV) == 4 ? 3 : BIG ? 2 : 8;
@@ -286,7 +287,7 @@ void fp_cyl_kernel(RayGrid g, CylGrid c,
                                                               TS *__restrict__ out, FpExtra ex) {
     TileCoord t = tile_coord(g);
     if (!t.valid) return;  // uniform over the block
-    if constexpr (BIG) t = square_waves(t);
+    if constexpr (sizeof(TV) == 2) t = square_waves(t);
     const bool active = t.iu < g.n_u && t.iv < g.n_v;
     float y = 0.0f;
     if (active) y = cyl_march<TV, MODE>(g, c, vol, ex, t);
