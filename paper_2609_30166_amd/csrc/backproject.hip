@@ -34,6 +34,7 @@
 // order, when several chunks share a brick).
 
 #include "ray_common.h"
+#include "warp_bounds.h"
 
 #include <algorithm>
 #include <climits>
@@ -661,33 +662,10 @@ struct NodeBox {
     int nx, ny, nz;    // nodes
 };
 
-// How far (voxels) a walked sample may lie outside its brick's box: the
-// range estimate's margins of 1/64 + 2^-20 i samples (i steps are at most the
-// hull's diagonal) and of 2^-22 of the largest side.
-__host__ __device__ inline double range_slack(const RayGrid &g) {
-    return g.step / 64.0 + (static_cast<double>(g.nx) + g.ny + g.nz) * 0x1p-19;
-}
-
-// Rounding of an FP32 node coordinate of an axis of gn nodes, generously.
-__host__ __device__ inline double node_slack(int gn) { return 1e-3 + gn * 0x1p-20; }
-
-// Nodes that the lookups of positions in [lo - M, hi + M], clipped to the
-// hull, can touch on an axis of n voxels and gn nodes at `scale` nodes per
-// voxel.
-__host__ __device__ inline void node_range(double lo, double hi, double M, int n, int gn,
-                                           double scale, int &first, int &count) {
-    const double a = fmax(lo - M, 0.0) * scale - node_slack(gn);
-    const double b = fmin(hi + M, n - 1.0) * scale + node_slack(gn);
-    const int i0 = static_cast<int>(fmin(fmax(floor(a), 0.0), gn - 2.0));
-    const int i1 = static_cast<int>(fmin(fmax(floor(b), 0.0), gn - 2.0)) + 1;
-    first = i0;
-    count = i1 - i0 + 1;
-}
-
 __device__ inline NodeBox brick_nodes(const WarpGrid &w, const RayGrid &g, int x0, int y0, int z0,
                                       int ex, int ey, int ez) {
     NodeBox b;
-    const double M = w.margin + range_slack(g);
+    const double M = walk_margin(w.margin, g.step, g.nx, g.ny, g.nz);
     node_range(x0, x0 + ex, M, g.nx, w.gx, w.sx, b.x0, b.nx);
     node_range(y0, y0 + ey, M, g.ny, w.gy, w.sy, b.y0, b.ny);
     node_range(z0, z0 + ez, M, g.nz, w.gz, w.sz, b.z0, b.nz);
@@ -696,7 +674,7 @@ __device__ inline NodeBox brick_nodes(const WarpGrid &w, const RayGrid &g, int x
 
 // Whether every brick's nodes fit in LDS (on each axis the most over the bricks).
 bool brick_nodes_fit(const WarpGrid &w, const RayGrid &g, const BrickGrid &bg) {
-    const double M = w.margin + range_slack(g);
+    const double M = walk_margin(w.margin, g.step, g.nx, g.ny, g.nz);
     auto most = [&](int size, int bricks, int n, int gn, double scale) {
         int m = 0;
         for (int k = 0; k < bricks; ++k) {
@@ -826,7 +804,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, 4))) vo
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const float p = tau * un[a], q = tau * ux[a];
-            const float e = WARP ? 1e-5f * (1.0f + fabsf(p) + fabsf(q)) : 0.0f;
+            const float e = WARP ? WALK_ROUND * (1.0f + fabsf(p) + fabsf(q)) : 0.0f;
             lo[a] = lo0[a] - fmaxf(p, q) - e;
             hi[a] = hi0[a] - fminf(p, q) + e;
         }
