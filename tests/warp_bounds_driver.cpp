@@ -1,7 +1,8 @@
 // Checks on the CPU that the nodes a warped brick keeps hold every lookup of
 // the samples it walks: for the outermost starting positions, formed as the
-// kernel forms its bounds, on axes of few and of many nodes per voxel and up to
-// the largest displacement, 64 voxels.  Ends with 1 at the first miss.
+// kernel forms its bounds, on axes of up to 330 nodes (LDS holds 1320 of a
+// brick, at least two on each of the other axes) and for displacements up to the
+// largest, 64 voxels.  Ends with 1 at the first miss.
 #include <algorithm>
 #include <cstdio>
 
