@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "ctrex_internal.h"
 
@@ -258,11 +259,20 @@ __global__ __launch_bounds__(NT) void conv3_c1_tile_kernel(const u16 *__restrict
 // Tiles: 8 x 4 rows for 16 outputs, 8 x 2 otherwise (16 -> 32 measured 0.83 ->
 // 0.70 ms as a data gradient at 256^3 with 8 x 2, 16 -> 16 0.46 -> 0.49 ms, so
 // each keeps its faster shape).
-template <int CIN, int COUT> struct ConvTile {
-    static constexpr int TY = 8, TZ = COUT == 16 ? 4 : 2;
+//
+// Volumes of fewer than 384 tiles of four planes (32 -> 16) take two, as each
+// workgroup then does half as much and CUs would idle otherwise: 32^3 (64 / 128
+// workgroups) 10.6 / 7.9 us, 48^3 (216 / 432) 11.7 / 10.5, 64^3 (512 / 1024) 15.5
+// / 20.4.
+template <int CIN, int COUT> constexpr int conv_planes() { return COUT == 16 ? 4 : 2; }
+constexpr long long FEW_TILES = 384;
+
+template <int CIN, int COUT, int PLANES> struct ConvTile {
+    static constexpr int TY = 8, TZ = PLANES;
     static constexpr int NW = CIN == 16 || COUT == 16 ? 1 : 2;   // waves over the outputs
     static constexpr int NB = COUT / 16 / NW;   // 16-channel output blocks per wave
-    static constexpr int WAVES = CIN == 16 ? (COUT == 16 ? 4 : 1) : (COUT == 32 ? 3 : 2);
+    static constexpr int WAVES =
+        CIN == 16 ? (COUT == 16 ? 4 : 1) : (COUT == 64 || (COUT == 16 && PLANES == 4) ? 2 : 3);
 };
 
 // Second input and output of a convolution over a channel concatenation: input
@@ -293,18 +303,20 @@ struct HeadArgs {
     int write_act;
 };
 
-template <int CIN, int COUT, bool OUT_F32, bool RELU, bool ACC, bool CAT>
+template <int CIN, int COUT, bool OUT_F32, bool RELU, bool ACC, bool CAT,
+          int PLANES = conv_planes<CIN, COUT>()>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(
-    ConvTile<CIN, COUT>::WAVES))) void
+    ConvTile<CIN, COUT, PLANES>::WAVES))) void
 conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *__restrict__ wt,
                   const float *__restrict__ bias, void *out, int out_cs, int out_off, int D, int H,
                   int W, int out_vec, CatArgs cat, HeadArgs head) {
-    constexpr int TY = ConvTile<CIN, COUT>::TY, TZ = ConvTile<CIN, COUT>::TZ;
+    using Tile = ConvTile<CIN, COUT, PLANES>;
+    constexpr int TY = Tile::TY, TZ = Tile::TZ;
     constexpr int CST = CIN < 32 ? CIN : 32;  // channels staged at a time
     constexpr int NH = CIN / CST;             // staging passes
     constexpr int SX = 18, SY = TY + 2, SZ = TZ + 2, NC = CST / 8;
     constexpr int NEL = SZ * SY * NC * SX;   // 16-byte elements
-    constexpr int NW = ConvTile<CIN, COUT>::NW, NB = ConvTile<CIN, COUT>::NB;
+    constexpr int NW = Tile::NW, NB = Tile::NB;
     constexpr int MBW = TY * TZ / (NT / 64 / NW);  // rows per wave
     static_assert(TY % MBW == 0, "a wave's rows lie in one z plane");
     __shared__ bf16x8 tile[NEL];
@@ -1568,22 +1580,35 @@ hipError_t conv3_go(hipStream_t s, const u16 *ip, int in_cs, int in_off, const u
                            dim3(static_cast<unsigned>(tiles)), dim3(NT), 0, s, ip, in_cs, in_off,
                            wp, bias, out, out_cs, out_off, D, H, W, out_vec);
     } else {
-        constexpr int TY = ConvTile<CI, CO>::TY, TZ = ConvTile<CI, CO>::TZ;
-        const long long tiles = static_cast<long long>((W + 15) / 16) * ((H + TY - 1) / TY) *
-                                ((D + TZ - 1) / TZ);
-        const dim3 grid(static_cast<unsigned>(tiles));
-        if (two_in) {
-            if constexpr (cat_shape<CI, CO>())
-                hipLaunchKernelGGL((conv3_tile_kernel<CI, CO, F32, RELU, ACC, true>), grid,
+        auto tiles = [&](int ty, int tz) {
+            return static_cast<long long>((W + 15) / 16) * ((H + ty - 1) / ty) * ((D + tz - 1) / tz);
+        };
+        auto launch = [&](auto planes) -> hipError_t {
+            constexpr int P = decltype(planes)::value;
+            const dim3 grid(static_cast<unsigned>(tiles(ConvTile<CI, CO, P>::TY, P)));
+            if (two_in) {
+                if constexpr (cat_shape<CI, CO>())
+                    hipLaunchKernelGGL((conv3_tile_kernel<CI, CO, F32, RELU, ACC, true, P>), grid,
+                                       dim3(NT), 0, s, ip, in_cs, in_off, wp, bias, out, out_cs,
+                                       out_off, D, H, W, out_vec, cat, head);
+                else
+                    return hipErrorInvalidValue;
+            } else {
+                hipLaunchKernelGGL((conv3_tile_kernel<CI, CO, F32, RELU, ACC, false, P>), grid,
                                    dim3(NT), 0, s, ip, in_cs, in_off, wp, bias, out, out_cs,
                                    out_off, D, H, W, out_vec, cat, head);
-            else
-                return hipErrorInvalidValue;
-        } else {
-            hipLaunchKernelGGL((conv3_tile_kernel<CI, CO, F32, RELU, ACC, false>), grid, dim3(NT),
-                               0, s, ip, in_cs, in_off, wp, bias, out, out_cs, out_off, D, H, W,
-                               out_vec, cat, head);
-        }
+            }
+            return hipSuccess;
+        };
+        constexpr int P = conv_planes<CI, CO>();
+        hipError_t e;
+        if constexpr (CI == 32 && CO == 16)
+            e = tiles(ConvTile<CI, CO, P>::TY, P) < FEW_TILES
+                    ? launch(std::integral_constant<int, 2>{})
+                    : launch(std::integral_constant<int, P>{});
+        else
+            e = launch(std::integral_constant<int, P>{});
+        if (e != hipSuccess) return e;
     }
     return hipGetLastError();
 }
