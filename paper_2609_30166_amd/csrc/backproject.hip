@@ -20,8 +20,8 @@
 // result does not depend on the order of the atomics).  A scale bounded from
 // max|r| puts the largest possible contribution at 2^30, so each one is a
 // 32-bit integer (weights formed in FP32, rounded to the nearest unit) while
-// the 64-bit sums cannot overflow.  For every (projection, sub-view) it bounds the detector pixels whose rays can reach
-// the brick (the projection of the brick grown by one voxel and the warp
+// the 64-bit sums cannot overflow.  For every (projection, sub-view) it bounds
+// the detector pixels whose rays can reach the brick (the projection of the brick grown by one voxel and the warp
 // bound), redoes those rays' FP64 set-up, clips their sample range to the
 // grown brick, and adds its eight corners with LDS 64-bit integer atomics.
 // The LDS brick carries one halo cell on each side in x and y, which takes
@@ -238,6 +238,7 @@ __attribute__((amdgpu_waves_per_eu(WARP ? 6 : 4, WARP ? 6 : 4))) void bp_brick_k
                                                               const float *__restrict__ rmax,
                                                               float *__restrict__ vol,
                                                               BrickGrid bg) {
+    static_assert(!OWN || WARP, "the unwarped owner form is bp_own_kernel");
     __shared__ unsigned long long acc[MAX_CELLS];
     constexpr int BP_THREADS = bp_threads<WARP>();
     constexpr bool TABLE = bp_table<WARP>();

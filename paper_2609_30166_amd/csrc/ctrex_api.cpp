@@ -255,9 +255,8 @@ struct SirtLayout {
 // The caller's scratch (ctrex_set_scratch), as the Cartesian projector calls
 // use it: the correction volume z, a 16-bit shadow, one region shared by the
 // gather copies of the forward projector (FP32: two pair-packed copies of 8
-// bytes per voxel; 16-bit: 4 bytes each) and the backprojector's
-// per-chunk partial volumes (never live at the same time), and the residual
-// partials.  Each call needs the prefix up to the last region it uses.
+// bytes per voxel; 16-bit: 4 bytes each) and the backprojector's 64-bit
+// integer volume (never live at the same time), and the residual partials.  Each call needs the prefix up to the last region it uses.
 struct ProjScratch {
     size_t z, shadow, shared, partials, total;
 };
@@ -340,7 +339,7 @@ CylScratch cyl_scratch(const ctrex_ctx *c) {
     return l;
 }
 
-// The same for a polar FP32 volume.
+// make_gather_copies of a polar FP32 volume.
 int make_polar_copies(ctrex_ctx *c, const float *vol, void *scratch, FpExtra &ex, hipStream_t s) {
     const CylScratch l = cyl_scratch(c);
     char *sc = static_cast<char *>(scratch);
@@ -1378,7 +1377,7 @@ int ctrex_sirt_iterate_cyl(ctrex_ctx *c, float *vol, const void *sino, int32_t s
     double *partials = reinterpret_cast<double *>(ws + L.partials);
     double *resid = reinterpret_cast<double *>(ws + L.resid);
     const size_t vox = static_cast<size_t>(c->cyl_nr) * c->cyl_nphi * c->cyl_nz;
-    // scratch: the correction volume z, then the pair-packed copy
+    // scratch: the pair-packed copies, and under them the correction volume z
     const CylScratch CL = cyl_scratch(c);
     void *scr;
     if ((st = ctx_scratch(c, CL.total, &scr)) != CTREX_OK) return st;
@@ -1415,7 +1414,6 @@ int ctrex_sirt_iterate_cyl(ctrex_ctx *c, float *vol, const void *sino, int32_t s
     std::vector<double> host_norms;
     if (resid_norms) host_norms.reserve(n_iter);
     FpExtra ex{sino, Rw, partials};
-
     for (int32_t k = 0; k < n_iter; ++k) {
         PhaseTimer t_fp{c, s, nullptr, 0}, t_bp{c, s, nullptr, 1}, t_up{c, s, nullptr, 2};
         CTREX_HIP(c, t_fp.begin());

@@ -82,8 +82,8 @@ struct PolarCorner {
     float fa, fb, fz;
 };
 
-// atan(t) / t - 1 over t^2 for t in [0, tan(pi/8)], relative error 6e-10 of
-// atan (minimax fit by Remez exchange).
+// atan(t) / t - 1 over t^2 for t in [0, tan(pi/8)], relative error 1.2e-9 of
+// atan, 1.4e-9 with the coefficients in FP32 (minimax fit by Remez exchange).
 __device__ __forceinline__ float atan_tail(float s) {
     float p = fmaf(s, -0.06034788f, 0.10573479f);
     p = fmaf(s, p, -0.14240083f);

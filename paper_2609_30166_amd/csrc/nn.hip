@@ -234,11 +234,11 @@ __global__ __launch_bounds__(NT) void conv3_c1_tile_kernel(const u16 *__restrict
 //
 // The weight reads bound these kernels: the four lanes of a quad read 16 bytes
 // of four different output channels, so one fragment takes the L1 about 32
-// accesses, for the MBW matrix instructions that it feeds (the address unit
-// was busy 63 to 77 % of the time).  So a wave takes 8 rows where it can, each
+// accesses, for the MBW matrix instructions that it feeds (four rows a wave kept
+// the address unit busy 63 to 77 % of the time).  So a wave takes 8 rows where it can, each
 // fragment feeding 8 instructions: with 32 or 64 outputs (and 32 or 64 inputs)
-// the four waves split NW = 2 ways over the output channels and 2 ways over the rows, with
-// 32 -> 16 the tile has four planes.  Times at 256^3 (64 -> 64: the 64^3
+// the four waves split NW = 2 ways over the output channels and 2 ways over the
+// rows, with 32 -> 16 the tile has four planes.  Times at 256^3 (64 -> 64: the 64^3
 // level of it), 4 rows a wave and now: 32 -> 16 of a concatenation 985 and 880
 // us, 64 -> 32 of one 525 and 340, 32 -> 32 182 and 138, 64 -> 64 133 and 86,
 // 32 -> 64 58 and 37.  16 -> 32 did not gain (89 and 96 us) and keeps all
@@ -248,8 +248,8 @@ __global__ __launch_bounds__(NT) void conv3_c1_tile_kernel(const u16 *__restrict
 // channels, an x's two chunks side by side in LDS (no bank conflicts) took
 // 16 -> 16 from 453 to 413 us, yet the training step at 128^3 from 2053 to 2070.
 //
-// More than 32 input channels are staged and contracted 32 at a time (the tile keeps the 32-channel shape and LDS
-// size: 64 channels at once would need a 4 x 2 tile, three times as many
+// More than 32 input channels are staged and contracted 32 at a time (the tile
+// keeps the 32-channel shape and LDS size: 64 channels at once would need a 4 x 2 tile, three times as many
 // halo voxels per output, and half the workgroups per CU).  Occupancy hints:
 // 16 -> 16 runs 4 waves per SIMD in 128 registers; 32 or 64 inputs with 32
 // outputs run 3 (the LDS tile admits three workgroups per CU), 32 -> 16 runs
@@ -575,10 +575,9 @@ conv3_tile_kernel(const u16 *__restrict__ in, int in_cs, int in_off, const u16 *
             continue;
         }
         // the gate's 4 channels of each row (one 8-byte load: stride and
-        // offset are multiples of 8); with at most 32 outputs those of all
-        // rows of the block are loaded together, so their latencies overlap
-        // (the 64-output tiles have no registers to spare for them)
-        constexpr int GB = NB <= 2 ? MBW : 1;   // rows per batch of gate loads
+        // offset are multiples of 8); those of all rows of the block are
+        // loaded together, so their latencies overlap
+        constexpr int GB = MBW;   // rows per batch of gate loads
 #pragma unroll
         for (int m0 = 0; m0 < MBW; m0 += GB) {
             uint2 gv[GB];

@@ -284,8 +284,8 @@ __device__ __forceinline__ float3 displacement(const WarpGrid &w, NodeCell &cell
 // for bit.
 template <bool WARP>
 __device__ __forceinline__ bool sample_corner(const VolDims &d, const WarpGrid &w, NodeCell &cell,
-                                              float tau, long long px, long long py, long long pz, int &ix,
-                                              int &iy, int &iz, float &fx, float &fy,
+                                              float tau, long long px, long long py, long long pz,
+                                              int &ix, int &iy, int &iz, float &fx, float &fy,
                                               float &fz) {
     int kx, ky, kz;
     float lx, ly, lz;
@@ -304,10 +304,10 @@ __device__ __forceinline__ bool sample_corner(const VolDims &d, const WarpGrid &
         fx = lx - ex;
         fy = ly - ey;
         fz = lz - ez;
-        const bool cell = static_cast<unsigned>(ix) <= static_cast<unsigned>(d.nx - 2) &&
-                          static_cast<unsigned>(iy) <= static_cast<unsigned>(d.ny - 2) &&
-                          static_cast<unsigned>(iz) <= static_cast<unsigned>(d.nz - 2);
-        if (cell) return true;
+        if (static_cast<unsigned>(ix) <= static_cast<unsigned>(d.nx - 2) &&
+            static_cast<unsigned>(iy) <= static_cast<unsigned>(d.ny - 2) &&
+            static_cast<unsigned>(iz) <= static_cast<unsigned>(d.nz - 2))
+            return true;
         // on the last face (weight 1 on the last cell's upper corner), or
         // outside the hull
         const bool in = axis_last(ix, fx, d.nx) & axis_last(iy, fy, d.ny) & axis_last(iz, fz, d.nz);
@@ -329,10 +329,10 @@ struct TileCoord {
     bool valid; // the pair exists
 };
 
-// XCD-aware block -> (tile, projection) mapping.  Hardware hands workgroup b
-// to XCD b mod 8.  The pairs are cut into units of g.grp consecutive
-// projections of g.run consecutive tiles (u fastest), projections fastest,
-// which the XCDs take in turn.  One unit's rays sample one part of the volume
+// XCD-aware block -> (tile, projection) mapping (launch_order, pair_of).
+// Hardware hands workgroup b to XCD b mod 8.  The pairs are cut into units of
+// g.grp consecutive projections of g.run consecutive tiles (u fastest),
+// projections fastest, which the XCDs take in turn.  One unit's rays sample one part of the volume
 // at nearly the same angle, so it stays in the XCD's 4 MB L2 while they march
 // (with all projections of a tile first, the XCD's ~100 concurrent workgroups
 // span 50 degrees or more of a scan); taking units in turn keeps the XCDs

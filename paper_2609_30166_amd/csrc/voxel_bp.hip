@@ -16,8 +16,8 @@
 // projected in FP64 (a, b, w) = P (X, 1).  When the depth row of P has no
 // z coefficient (every circular orbit about z), w is the same for the whole
 // column and u_k = u_0 + k P[0][2] / w: the integer parts of u_0 and v_0 are
-// taken in FP64 and the remainders plus k du in FP32 (|k du| < KZ pixels,
-// so positions stay within about 1e-6 pixel).  Otherwise, or when the
+// taken in FP64 and the remainders plus k du in FP32 (within a footprint under
+// 49 pixels, so positions stay within about 3e-6 pixel).  Otherwise, or when the
 // column's numbers are huge, each voxel is projected in FP64 on its own.
 //
 // Detector lookups (vbp_tile_kernel): four global loads per voxel and view,
@@ -26,7 +26,7 @@
 // footprint of the patch and copies it to LDS (zeros outside the image, which
 // also makes the borders need no code), and all four waves then sample the
 // four footprints: two LDS reads per voxel and 13 VALU instructions, the bound.
-// 360 views of 384^2 at 256^3: 7.36 -> 3.69 ms (without the footprints, but
+// 360 views of 384^2 at 256^3: 7.36 -> 3.59 ms (without the footprints, but
 // with a path of 13 instructions per voxel for columns inside the image: 6.2).
 // Four waves per SIMD: at 3 (no spills) 4.2 ms, at 5 (spills) 14.  A view
 // whose footprint does not fit, or whose depth row has a z coefficient, is
