@@ -81,14 +81,15 @@ LDS_ATOMIC_PEAK_TOPS = 256 * 16 * 2.4e9 / 1e12
 # algorithmic VALU lane operations per sample (position 3 FMA; floor, convert
 # and fraction per axis 9; clamps and address 5; blend 14 or 8 weights and
 # their fixed-point conversion; accumulate 1)
-# ("bp_brick_kernel" names the row of the exact backprojection, whose default
-# form is bp_own_kernel)
+# (the row "bp_brick_kernel" is the exact backprojection, whose default form is
+# bp_own_kernel, and "vbp_kernel" the voxel-driven one, vbp_tile_kernel)
 ALU_OPS = {"fp_kernel": 32, "bp_brick_kernel": 44}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_sirt_512cube_720x768sq.md")
 WEIGHTS_FILE = os.path.join(ROOT, "paper_2609_30166_amd", "weights", "unet_learned_256.npz")
 KERNEL_SOURCES = {
-    "bp_brick_kernel": ["backproject.hip", "ray_common.h", "ctrex_internal.h"],
-    "fp_kernel": ["projector.hip", "ray_common.h", "ctrex_internal.h"],
+    "bp_brick_kernel": ["backproject.hip", "ray_common.h", "ctrex_internal.h", "launch_order.h",
+                        "warp_bounds.h"],
+    "fp_kernel": ["projector.hip", "ray_common.h", "ctrex_internal.h", "launch_order.h"],
     "vbp_kernel": ["voxel_bp.hip", "ray_common.h", "ctrex_internal.h"],
 }
 
