@@ -234,9 +234,10 @@ __global__ __launch_bounds__(NT) void conv3_c1_tile_kernel(const u16 *__restrict
 //
 // The weight reads bound these kernels: the four lanes of a quad read 16 bytes
 // of four different output channels, so one fragment takes the L1 about 32
-// accesses, for the MBW matrix instructions that it feeds (four rows a wave kept
-// the address unit busy 63 to 77 % of the time).  So a wave takes 8 rows where it can, each
-// fragment feeding 8 instructions: with 32 or 64 outputs (and 32 or 64 inputs)
+// accesses, for the MBW matrix instructions that it feeds (with four rows a
+// wave the address unit was busy 72 % of the time in 32 -> 16 of a concatenation
+// and 86 % in 64 -> 32 of one; now 51 and 70 %).  So a wave takes 8 rows where it
+// can, each fragment feeding 8 instructions: with 32 or 64 outputs (and 32 or 64 inputs)
 // the four waves split NW = 2 ways over the output channels and 2 ways over the
 // rows, with 32 -> 16 the tile has four planes.  Times at 256^3 (64 -> 64: the 64^3
 // level of it), 4 rows a wave and now: 32 -> 16 of a concatenation 985 and 880
