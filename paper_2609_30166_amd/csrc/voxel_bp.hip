@@ -31,7 +31,7 @@
 // Four waves per SIMD: at 3 (no spills) 4.2 ms, at 5 (spills) 14.  A view
 // whose footprint does not fit, or whose depth row has a z coefficient, is
 // sampled from global memory with the border handling; geometries in which more
-// than a tenth are take vbp_kernel, which does nothing else (footprint_column).
+// than a quarter are take vbp_kernel, which does nothing else (footprint_column).
 
 #include "ray_common.h"
 
@@ -47,9 +47,10 @@ constexpr int VB_TY = 16;
 constexpr int VB_THREADS = VB_TX * VB_TY;
 constexpr int FT_U = 49, FT_V = 36;    // largest footprint; an odd row stride
 constexpr int FT_N = VB_THREADS / 64;  // views per round, one per wave
-// Footprints are bounded in FP32, whose spacing is 1/128 below this pixel; one
-// further out is sampled from memory, where columns come from FP64.
-constexpr float FAR_PIXEL = 131072.0f;
+// Footprints are bounded in FP32, whose spacing is 1/128 below pixel 2^17; one
+// that starts further out than this is sampled from memory, where columns come
+// from FP64.
+constexpr float FAR_PIXEL = 131072.0f - 64.0f;
 
 typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -353,8 +354,8 @@ vbp_tile_kernel(
             const double w = fma(M[8], bx, fma(M[9], by, fma(M[10], bz, M[11])));
             const unsigned long long pos = __ballot(w > 0.0), neg = __ballot(w < 0.0);
             const double r = 1.0 / w;
-            // 0.01 pixel covers the FP32 rounding here (two of 1/256 at most
-            // up to FAR_PIXEL) and of the samples' offsets within a column
+            // 0.01 pixel covers the FP32 rounding here (two of 1/256 at most up
+            // to FAR_PIXEL and a footprint) and of the samples' offsets within a column
             const float u = static_cast<float>(a * r), v = static_cast<float>(b * r);
             const float ua = floorf(min8(u) - 0.01f), ub = floorf(0.01f - min8(-u)) + 1.0f;
             const float va = floorf(min8(v) - 0.01f), vb = floorf(0.01f - min8(-v)) + 1.0f;
@@ -362,8 +363,7 @@ vbp_tile_kernel(
             // coefficient in the depth row; the corners bound the patch only
             // if it lies on one side of the source plane
             const bool fits = M[10] == 0.0 && (~pos == 0 || ~neg == 0) && ub - ua < FT_U &&
-                              vb - va < FT_V && ua > -FAR_PIXEL && ub < FAR_PIXEL &&
-                              va > -FAR_PIXEL && vb < FAR_PIXEL;
+                              vb - va < FT_V && fabsf(ua) < FAR_PIXEL && fabsf(va) < FAR_PIXEL;
             Footprint f{0, 0, 2, 0};
             if (fits) {   // uniform
                 f.u0 = __builtin_amdgcn_readfirstlane(static_cast<int>(ua));
@@ -546,14 +546,13 @@ bool footprint_fits(const double *M, const VoxelGrid &vg, int tx, int ty, int nx
 }  // namespace
 
 // With a footprint a view costs vbp_tile_kernel half of what it costs
-// vbp_kernel, without one one and a half to twice as much, and patches that lack
-// many hold the launch up: up to a tenth may lack it.  60 views of 384^2 at
-// 256^3, vbp_tile_kernel and vbp_kernel: 606 and 1218 us with footprints,
-// jittered (none has one) 2609 and 2070, of 768^2 (too large) 1927 and 1252;
-// 2 x 512 x 512 (z, y, x) jittered 139 and 100; cylinder of 150 x 400 x 100, of
-// whose outer patches half lack it, 744 and 506, 150 x 500 x 100 (a sixth) 723
-// and 649, 100 x 400 x 150 (a twentieth) 416 and 506.  A single view has too few
-// loads in flight (256^3: 36 and 31 us).
+// vbp_kernel, without one a tenth to twice more, and patches that lack many hold
+// the launch up: up to a quarter may lack it.  60 views of 384^2 at 256^3,
+// vbp_tile_kernel and vbp_kernel: 606 and 1218 us with footprints, jittered
+// (none has one) 2609 and 2090, of 768^2 (too large) 1401 and 1250; 2 x 512 x 512
+// (z, y, x) jittered 139 and 101; cylinder of 150 x 400 x 100 (27 % lack it) 535
+// and 508, 150 x 500 x 100 (16 %) 553 and 651, 100 x 400 x 150 (6 %) 367 and 508.
+// A single view has too few loads in flight (256^3: 36 and 31 us).
 int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz) {
     // the middle patches of a division into 3 x 3
     const int px = (nx - 1) / VB_TX + 1, py = (ny - 1) / VB_TY + 1;
@@ -569,7 +568,7 @@ int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int
                 miss += !footprint_fits(P + 12 * k, vg, (2 * (i % 3) + 1) * px / 6,
                                         (2 * (i / 3) + 1) * py / 6, nx, ny, nz, kz);
             }
-        if (10 * miss <= all) return kz;
+        if (4 * miss <= all) return kz;
     }
     return 0;
 }
