@@ -517,12 +517,10 @@ hipError_t launch_typed(const RayGrid &g, const double *Pm, const void *sino, fl
                : launch_columns<TS, 4, false>(g, Pm, src, vol, accumulate, vg, s);
 }
 
-// Whether a view's footprint of the patch (tx, ty), kz voxels about the middle
-// of the volume, fits in LDS (vbp_tile_kernel's rule).
-bool footprint_fits(const double *M, const VoxelGrid &vg, int tx, int ty, int nx, int ny, int nz,
-                    int kz) {
+// Whether a view's footprint of a patch, kz voxels about the middle of the
+// volume, fits in LDS (vbp_tile_kernel's rule).
+bool footprint_fits(const double *M, const VoxelGrid &vg, const PatchBox &b, int kz) {
     if (M[10] != 0.0) return false;
-    const PatchBox b = patch_box(vg, tx, ty, nx, ny, nz);
     const double dz = vg.cyl ? vg.dz : 1.0, hz = 0.5 * (kz - 1) * dz;
     double u0 = FAR_PIXEL, u1 = -FAR_PIXEL, v0 = FAR_PIXEL, v1 = -FAR_PIXEL;
     bool pos = true, neg = true;
@@ -556,6 +554,9 @@ bool footprint_fits(const double *M, const VoxelGrid &vg, int tx, int ty, int nx
 int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int ny, int nz) {
     // the middle patches of a division into 3 x 3
     const int px = (nx - 1) / VB_TX + 1, py = (ny - 1) / VB_TY + 1;
+    PatchBox box[9];
+    for (int i = 0; i < 9; ++i)
+        box[i] = patch_box(vg, (2 * (i % 3) + 1) * px / 6, (2 * (i / 3) + 1) * py / 6, nx, ny, nz);
     const size_t step = (m + 63) / 64;
     bool upright = true;
     for (size_t k = 0; k < m; k += step) upright = upright && P[12 * k + 2] == 0.0;
@@ -563,10 +564,9 @@ int footprint_column(const double *P, size_t m, const VoxelGrid &vg, int nx, int
     for (int kz = longest; kz >= std::min(longest, 8); kz /= 2) {
         size_t all = 0, miss = 0;
         for (size_t k = 0; k < m; k += step)
-            for (int i = 0; i < 9; ++i) {
+            for (const PatchBox &b : box) {
                 ++all;
-                miss += !footprint_fits(P + 12 * k, vg, (2 * (i % 3) + 1) * px / 6,
-                                        (2 * (i / 3) + 1) * py / 6, nx, ny, nz, kz);
+                miss += !footprint_fits(P + 12 * k, vg, b, kz);
             }
         if (4 * miss <= all) return kz;
     }
